@@ -28,6 +28,10 @@ template <bool V>
 struct bool_constant {
   static constexpr bool value = V;
 };
+template <int V>
+struct int_constant {
+  static constexpr int value = V;
+};
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
@@ -231,6 +235,15 @@ struct Tile {
   static constexpr int NW = BN / WN;  // columns per wave
   static constexpr int TM = MW / 16;
   static constexpr int TN = NW / 16;
+  // The quadrant tile: 256 rows over eight waves with a two-stage ring runs
+  // the ping-pong mainloop (below), whose waves own 64 x 32 blocks of the four
+  // 128 x 128 quadrants instead of one contiguous block.
+  static constexpr bool QUAD = BM == 256 && WM == 2 && WN == 4 && NS == 2 && BK_ == 64 && (BN == 128 || BN == 256);
+  // First row of row block tm, and first column of block pair tp, of the wave at (wm, wn).
+  __device__ static constexpr int row_of(int wm, int tm) {
+    return QUAD ? 64 * wm + 16 * (tm & 3) + 128 * (tm >> 2) : wm * MW + 16 * tm;
+  }
+  __device__ static constexpr int col_of(int wn, int tp) { return QUAD ? 32 * wn + 128 * tp : wn * NW + 32 * tp; }
   static_assert(TM >= 1 && TN >= 2 && TN % 2 == 0, "wave tile shape");
   static constexpr int A_BYTES = BM * BK * 2;
   static constexpr int B_BYTES = BK * BN * 2;
@@ -359,11 +372,268 @@ struct NoCheck {
   __device__ __forceinline__ void operator()(X...) {}
 };
 
+// The mainloop of the quadrant tile (Tile::QUAD): 256 rows by two column halves
+// of 128 (one 256-column operand, or two 128-column ones), eight waves, two
+// waves to a SIMD.
+//
+// What bounds it: a 64-deep stage is 2048 cycles of MFMA per SIMD, and its
+// fragment reads and direct-to-LDS writes keep the LDS busy about three
+// quarters of that time.  With every wave reading its fragments after one barrier and the
+// whole next stage requested only then, neither side overlapped: 3700 cycles
+// a stage.  Here the two waves of a SIMD alternate instead (waves 0-3 run half
+// a phase ahead of waves 4-7): while one multiplies, the other reads the
+// fragments of its next products and requests loads.
+//
+// A stage is four phases, one output quadrant (rows half a, columns half b)
+// of 64 x 32 per wave and 16 products each, in the order
+//   phase 0: (A0, B0)   1: (A0, B1)   2: (A1, B1)   3: (A1, B0)
+// and a phase is a memory slot and a product slot, each ended by a barrier:
+//   memory slot 0 of stage it: request A1 of stage it + 1, read B0 of stage it
+//               1:             request A0 of it + 2,       read B1 of it
+//               2:             request B0 of it + 2,       read A1 of it
+//               3:             request B1 of it + 2,       read A0 of it + 1
+// Each half tile is requested six phases before it is read, so five half
+// tiles (80 KB of the 128 KB ring) stay in flight and no wait drains them.
+//   * Visibility: a wave waits for its own pieces of a half tile at the end
+//     of the memory slot before the one that reads it.  The trailing waves
+//     reach that wait one slot before the leading waves read, and a barrier
+//     lies between.
+//   * Reuse: a half tile read in memory slot p is complete in registers at
+//     product slot p (lgkmcnt(0)), and its ring slot is requested again in
+//     memory slot p + 2.  The trailing waves' product slot p ends, with a
+//     barrier, before the leading waves' memory slot p + 2 begins.
+// An item that may have to wait for its activation rows: wave 0 waits in
+// memory slot 0 for the rows of stage it + 2, which no wave requests before
+// the barrier that ends the slot, so that barrier is the broadcast.
+//
+// Measured against the plain two-stage loop (pipelined mode): 8192 rows
+// through 8192 x 8192 weights 1682 -> 1528 us (1.31 -> 1.44 PFLOP/s),
+// 2048 x 4096 x 14336 429 -> 396 us, gated 256 x 8192 x 28672 374 -> 339 us.
+//
+// The products of one output run in the same order as in the plain mainloop.
+template <class T, int NB, class Wait>
+__device__ __forceinline__ void mainloop_quad(const uint16_t* __restrict__ A, long lda, int m0, int mlast,
+                                              const uint16_t* const (&Bp)[NB], long ldb, int n0, int kbeg, int kend,
+                                              f32x4 (&acc)[NB][T::TN][T::TM], char* lds, Wait& wait, TraceAcc& tr) {
+  static_assert(T::QUAD && NB * T::BN == 256 && T::TM == 8 && NB * T::TN == 4 && T::NWAVES == 8, "quadrant tile");
+  int tid = threadIdx.x;
+  asm volatile("" : "+v"(tid));  // per-lane offsets are derived per call, as in the plain mainloop
+  const int lane = tid & 63;
+  const int wave = uniform(tid >> 6);
+  const int wm = wave % T::WM, wn = wave / T::WM;
+  const bool trailing = wave >= 4;
+
+#pragma unroll
+  for (int b = 0; b < NB; ++b)
+#pragma unroll
+    for (int i = 0; i < T::TN; ++i)
+#pragma unroll
+      for (int j = 0; j < T::TM; ++j) acc[b][i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  const int nk = (kend - kbeg) / 64;
+  if (nk <= 0) return;
+
+  constexpr uint32_t kHalf = 16384, kB = 2 * kHalf, kStage = 4 * kHalf;  // LDS: A0, A1, B0, B1 per stage
+  const uint32_t lds_base = (uint32_t)(uintptr_t)lds;
+
+  // Load sources: per-lane offsets from a per-stage uniform base.  A half: 128
+  // rows of 128 bytes, 8 to a 1 KB piece; B half: 64 rows of 256 bytes, 4 to a piece.
+  uint32_t a_off[4], b_off[2];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const int row = 8 * (wave + 8 * j) + lane / 8;
+    int gr = m0 + row;
+    gr = gr > mlast ? mlast : gr;
+    a_off[j] = (uint32_t)(((long)gr * lda + 8 * ((lane & 7) ^ swz_a<64>(row))) * 2);
+  }
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    const int row = 4 * (wave + 8 * j) + lane / 16;
+    b_off[j] = (uint32_t)(((long)row * ldb + 8 * ((lane & 15) ^ swz_b<128>(row))) * 2);
+  }
+  const uint16_t* pa = A + kbeg;
+  const uint16_t* pb[2];
+  pb[0] = Bp[0] + (long)kbeg * ldb + n0;
+  pb[1] = NB == 2 ? Bp[NB - 1] + (long)kbeg * ldb + n0 : pb[0] + 128;
+
+  auto load_a = [&](int half, int st) {
+    const uint32_t dst = lds_base + (uint32_t)(st & 1) * kStage + (uint32_t)half * kHalf + (uint32_t)wave * 1024u;
+#pragma unroll
+    for (int j = 0; j < 2; ++j) dma16(pa + (long)st * 64, a_off[2 * half + j], uniform(dst + 8192u * j));
+  };
+  auto load_b = [&](int half, int st) {
+    const uint32_t dst = lds_base + (uint32_t)(st & 1) * kStage + kB + (uint32_t)half * kHalf + (uint32_t)wave * 1024u;
+    const uint16_t* src = pb[half] + (long)st * 64 * ldb;
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      if constexpr (T::WNT) dma16_nt(src, b_off[j], uniform(dst + 8192u * j));
+      else dma16(src, b_off[j], uniform(dst + 8192u * j));
+    }
+  };
+
+  // Fragment addresses inside a stage (the plain mainloop's, per half tile).
+  const int arow = T::row_of(wm, 0) + (lane & 15);
+  uint32_t a_frag[2];
+#pragma unroll
+  for (int ks = 0; ks < 2; ++ks) a_frag[ks] = (uint32_t)(arow * 128 + (((4 * ks + (lane >> 4)) ^ swz_a<64>(arow)) << 4));
+  const int brow = 8 * (lane >> 4) + ((lane & 15) >> 2);
+  const uint32_t b_frag = kB + (uint32_t)(brow * 256 + (((4 * wn + (lane & 3)) ^ swz_b<128>(brow)) << 4));
+
+  bf16x8 xa[2][4], xb[2][4], w0[2][2], w1[2][2];
+  auto read_a = [&](bf16x8 (&x)[2][4], int half, int st) {
+    const char* base = lds + (st & 1) * kStage + half * kHalf;
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+      for (int tm = 0; tm < 4; ++tm) x[ks][tm] = *reinterpret_cast<const bf16x8*>(base + a_frag[ks] + tm * 2048);
+  };
+  auto read_b = [&](bf16x8 (&w)[2][2], int half, int st) {
+    const char* base = lds + (st & 1) * kStage + half * kHalf;
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        const char* p = base + b_frag + ks * 8192 + i * 8;
+        bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4_t*)(p));
+        bf16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4_t*)(p + 1024));
+        w[ks][i] = (bf16x8)__builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+      }
+  };
+  auto mma = [&](const bf16x8 (&w)[2][2], const bf16x8 (&x)[2][4], auto bh, auto ah) {
+    constexpr int b = decltype(bh)::value ? 1 : 0, a = decltype(ah)::value ? 4 : 0;
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int tm = 0; tm < 4; ++tm) {
+          f32x4& c = acc[NB == 2 ? b : 0][NB == 2 ? i : 2 * b + i][a + tm];
+          c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[ks][i], x[ks][tm], c, 0, 0, 0);
+        }
+  };
+  using Lo = bool_constant<false>;
+  using Hi = bool_constant<true>;
+
+  auto slot_end = [&]() {  // a barrier that neither the compiler's memory operations nor its products cross
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  auto vm_traced = [&](auto n) {
+    const uint64_t t0 = trace_now();
+    wait_vm<decltype(n)::value>();
+    if constexpr (kTrace) tr.ring += trace_now() - t0;
+  };
+  auto products_begin = [&]() {  // this wave's fragment reads are complete
+    __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_setprio(1);
+  };
+  auto products_end = [&]() {
+    __builtin_amdgcn_s_setprio(0);
+    slot_end();
+  };
+
+  // One stage.  LEFT: stages after it, counted up to 2 (fewer loads to request
+  // and to leave in flight).
+  auto stage = [&](int it, auto left_) {
+    constexpr int LEFT = decltype(left_)::value;
+    if constexpr (LEFT >= 1) load_a(1, it + 1);
+    read_b(w0, 0, it);
+    if constexpr (LEFT >= 2) {
+      const int k = kbeg + (it + 2) * 64;
+      if (Wait::kBlocks && wave == 0) wait.leader(k);
+      wait.known(k);
+    }
+    vm_traced(int_constant<LEFT >= 1 ? 10 : 2>());  // B1 of this stage
+    slot_end();
+    products_begin();
+    mma(w0, xa, Lo(), Lo());
+    products_end();
+
+    if constexpr (LEFT >= 2) load_a(0, it + 2);
+    read_b(w1, 1, it);
+    vm_traced(int_constant<LEFT >= 2 ? 10 : LEFT == 1 ? 8 : 0>());  // A1 of this stage
+    slot_end();
+    products_begin();
+    mma(w1, xa, Hi(), Lo());
+    products_end();
+
+    if constexpr (LEFT >= 2) load_b(0, it + 2);
+    read_a(xb, 1, it);
+    if constexpr (LEFT >= 1) vm_traced(int_constant<LEFT >= 2 ? 10 : 6>());  // A0 of the next stage
+    slot_end();
+    products_begin();
+    mma(w1, xb, Hi(), Hi());
+    products_end();
+
+    if constexpr (LEFT >= 2) load_b(1, it + 2);
+    if constexpr (LEFT >= 1) {
+      read_a(xa, 0, it + 1);
+      vm_traced(int_constant<LEFT >= 2 ? 10 : 4>());  // B0 of the next stage
+    }
+    slot_end();
+    products_begin();
+    mma(w0, xb, Lo(), Hi());
+    products_end();
+  };
+
+  // Prologue: the first stage and all of the second but A1.
+  const bool two = nk > 1;
+  if constexpr (Wait::kBlocks) {  // the weights stream while the item waits for its rows
+    load_b(0, 0);
+    load_b(1, 0);
+    if (two) {
+      load_b(0, 1);
+      load_b(1, 1);
+    }
+    if (wave == 0) {
+      wait.leader(kbeg);
+      if (two) wait.leader(kbeg + 64);
+    }
+    slot_end();
+    load_a(0, 0);
+    load_a(1, 0);
+    if (two) load_a(0, 1);
+    wait_vm<0>();  // requested out of the stage order, so nothing less covers it
+  } else {
+    load_a(0, 0);
+    load_b(0, 0);
+    load_b(1, 0);
+    load_a(1, 0);
+    if (two) {
+      load_a(0, 1);
+      load_b(0, 1);
+      load_b(1, 1);
+      wait_vm<10>();  // A0, B0
+    } else {
+      wait_vm<4>();
+    }
+  }
+  wait.known(kbeg);
+  if (two) wait.known(kbeg + 64);
+  slot_end();
+  read_a(xa, 0, 0);
+  __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
+
+  if (trailing) slot_end();
+  for (int it = 0; it < nk - 2; ++it) stage(it, int_constant<2>());
+  if (two) stage(nk - 2, int_constant<1>());
+  stage(nk - 1, int_constant<0>());
+  if (!trailing) slot_end();
+  __syncthreads();  // every wave is done reading the ring before it is reused
+}
+
 template <class T, int NB, class Wait, class Check = NoCheck>
 __device__ __forceinline__ void mainloop(const uint16_t* __restrict__ A, long lda, int m0, int mlast,
                                          const uint16_t* const (&Bp)[NB], long ldb, int n0, int kbeg, int kend,
                                          f32x4 (&acc)[NB][T::TN][T::TM], char* lds, Wait& wait, TraceAcc& tr,
                                          Check check = Check()) {
+  if constexpr (T::QUAD && NB * T::BN == 256 && is_same_type<Check, NoCheck>::value) {
+    mainloop_quad<T, NB>(A, lda, m0, mlast, Bp, ldb, n0, kbeg, kend, acc, lds, wait, tr);
+    return;
+  }
   // The thread index passes through an empty asm, so the compiler derives
   // this call's per-lane offsets here instead of hoisting them out of the
   // persistent item loop: in the pipelined kernel, whose items take one of
@@ -465,7 +735,7 @@ __device__ __forceinline__ void mainloop(const uint16_t* __restrict__ A, long ld
   //   weight (MFMA A operand): ds_read_b64_tr_b16 over 4 rows x 4 chunks per 16-lane group;
   //     lane 4r+c of group g addresses row 8g+r (+4 for the upper half), columns 8c + 4*t2 .. +3,
   //     and receives column (8*(i/4) + 4*t2 + i%4) of those 4 rows, i = lane % 16.
-  const int arow = wm * T::MW + (lane & 15);
+  const int arow = T::row_of(wm, 0) + (lane & 15);
   int a_frag[T::BK / 32];  // K half ks: chunk 4 ks + lane / 16 of the row
 #pragma unroll
   for (int ks = 0; ks < T::BK / 32; ++ks)
@@ -475,7 +745,7 @@ __device__ __forceinline__ void mainloop(const uint16_t* __restrict__ A, long ld
   int b_frag[T::TN / 2];
 #pragma unroll
   for (int tp = 0; tp < T::TN / 2; ++tp) {
-    const int q = ((wn * T::NW + 32 * tp) >> 3) + c4;
+    const int q = (T::col_of(wn, tp) >> 3) + c4;
     b_frag[tp] = T::A_BYTES + brow * (2 * T::BN) + ((q ^ swz_b<T::BN>(brow)) << 4);
   }
 
@@ -493,7 +763,7 @@ __device__ __forceinline__ void mainloop(const uint16_t* __restrict__ A, long ld
     return (bf16x8)__builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
   };
   auto act_frag = [&](const char* base, int ks, int tm) {
-    return *reinterpret_cast<const bf16x8*>(base + a_frag[ks] + tm * 16 * T::ROW_BYTES);
+    return *reinterpret_cast<const bf16x8*>(base + a_frag[ks] + T::row_of(0, tm) * T::ROW_BYTES);
   };
   auto compute = [&](int st) {
     const char* base = lds + (st % T::NS) * SB;
@@ -681,17 +951,17 @@ struct SentinelCheck {
 
 // ------------------------------------------------------------------ fragment <-> tile coordinates
 
-// Output coordinates held by this lane for block pair tp and row block tm:
-// row  = m0 + wm*MW + 16*tm + lane%16
-// cols = n0 + wn*NW + 32*tp + 8*(lane/16) + [0..8)
+// Output coordinates held by this lane for block pair tp and row block tm.
 template <class T>
 struct FragPos {
   int row0, col0;
   __device__ FragPos(int m0, int n0) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    row0 = m0 + (wave % T::WM) * T::MW + (lane & 15);
-    col0 = n0 + (wave / T::WM) * T::NW + 8 * (lane >> 4);
+    row0 = m0 + T::row_of(wave % T::WM, 0) + (lane & 15);
+    col0 = n0 + T::col_of(wave / T::WM, 0) + 8 * (lane >> 4);
   }
+  __device__ int row(int tm) const { return row0 + T::row_of(0, tm); }
+  __device__ int col(int tp) const { return col0 + T::col_of(0, tp); }
 };
 
 template <class T>
@@ -753,8 +1023,8 @@ struct Unit {
     tp = r - tm * (T::TN / 2);
   }
   // Output row and first of the 8 consecutive columns held by `lane` of this unit.
-  __device__ int row(int m0, int lane) const { return m0 + (w % T::WM) * T::MW + 16 * tm + (lane & 15); }
-  __device__ int col(int n0, int lane) const { return n0 + (w / T::WM) * T::NW + 32 * tp + 8 * (lane >> 4); }
+  __device__ int row(int m0, int lane) const { return m0 + T::row_of(w % T::WM, tm) + (lane & 15); }
+  __device__ int col(int n0, int lane) const { return n0 + T::col_of(w / T::WM, tp) + 8 * (lane >> 4); }
 };
 
 // v[g][b][0..7] = sum over s = 0 .. S-1 (in that order) of the 8 values of
@@ -873,6 +1143,7 @@ struct Claim {
 struct NoWait {
   static constexpr bool kBlocks = false;  // never waits
   __device__ __forceinline__ bool all_known() const { return true; }
+  __device__ __forceinline__ void leader(int) {}
   __device__ __forceinline__ void operator()(int) {}
 };
 
@@ -885,6 +1156,11 @@ struct ClaimAtLastStage {
   __device__ __forceinline__ bool all_known() const { return wait.all_known(); }
   __device__ __forceinline__ void operator()(int k) {
     wait(k);
+    known(k);
+  }
+  // The wait by wave 0 alone (ReadyWait::leader), and the claim.
+  __device__ __forceinline__ void leader(int k) { wait.leader(k); }
+  __device__ __forceinline__ void known(int k) {
     if (k == k_last) next->issue();
   }
 };
@@ -956,38 +1232,59 @@ struct ReadyWait {
     while (k_hi >= k_ready);
     if constexpr (kTrace) tr->flag += trace_now() - t0;
   }
-  // One poll-and-gather round from column block kb; updates k_ready.
+  // For a loop whose barriers already order the waves: wave 0 alone calls
+  // this before a barrier that every wave passes before it requests the
+  // stage's activation rows.  The barrier tells the others; k_ready is then
+  // wave 0's own.
+  __device__ __forceinline__ void leader(int k) {
+    const int k_hi = k + span - 1;
+    if (k_hi < k_ready) return;
+    const uint64_t t0 = trace_now();
+    do {
+      const int hi = poll((k > k_ready ? k : k_ready) / bn1);
+      k_ready = hi < 0 || hi >= kb_last ? 0x7fffffff : (hi + 1) * bn1;
+    } while (k_hi >= k_ready);
+    if constexpr (kTrace) tr->flag += trace_now() - t0;
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+  }
+  // One poll-and-gather round from column block kb, by one wave: the last
+  // block of the ready prefix, or -1 when the wait gave up.
+  __device__ __forceinline__ int poll(int kb) const {
+    const int lane = threadIdx.x & 63;
+    const int j = kb + lane;
+    int hi = -1;
+    if (uniform(ld_relaxed(err)) == 0u) {
+      // Poll the first counter needed, every lane at the same address (one
+      // request per poll: a long wait must not flood the memory side that
+      // the running producers stream from); scalar loop, uniform exits.
+      const uint32_t* first = ready + ((long)kb * Mb + mb) * kLine;
+      uint64_t m = 0;
+      for (uint32_t polls = 0;; ++polls) {
+        const uint32_t v = ld_relaxed(first);
+        m = __builtin_amdgcn_ballot_w64((int32_t)(v - target) >= 0);
+        if ((m & 1u) || polls >= spin_limit) break;
+        __builtin_amdgcn_s_sleep(2);
+      }
+      if (m & 1u) {
+        // then the longest ready prefix of up to 64 counters in one gather
+        // (counters only grow during a run, so the first is still ready)
+        const uint32_t v = ld_relaxed(ready + ((long)(j <= kb_last ? j : kb_last) * Mb + mb) * kLine);
+        m = __builtin_amdgcn_ballot_w64((j <= kb_last) & ((int32_t)(v - target) >= 0));
+        // ~m == 0 (all 64 ready) must be taken apart: a count of trailing
+        // zeros of 0 is undefined, and the scalar find-first-one the
+        // compiler emits for it returns -1.
+        hi = ~m ? kb + (int)__builtin_ctzll(~m) - 1 : kb + 63;
+      } else if (lane == 0) {
+        __hip_atomic_fetch_or(err, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
+    }
+    return hi;
+  }
+  // The round for every wave: wave 0 polls and broadcasts; updates k_ready.
   __device__ __forceinline__ void acquire(int kb) {
     if (uniform((int)(threadIdx.x >> 6)) == 0) {  // wave 0, as a scalar branch
-      const int lane = threadIdx.x & 63;
-      const int j = kb + lane;
-      int hi = -1;
-      if (uniform(ld_relaxed(err)) == 0u) {
-        // Poll the first counter needed, every lane at the same address (one
-        // request per poll: a long wait must not flood the memory side that
-        // the running producers stream from); scalar loop, uniform exits.
-        const uint32_t* first = ready + ((long)kb * Mb + mb) * kLine;
-        uint64_t m = 0;
-        for (uint32_t polls = 0;; ++polls) {
-          const uint32_t v = ld_relaxed(first);
-          m = __builtin_amdgcn_ballot_w64((int32_t)(v - target) >= 0);
-          if ((m & 1u) || polls >= spin_limit) break;
-          __builtin_amdgcn_s_sleep(2);
-        }
-        if (m & 1u) {
-          // then the longest ready prefix of up to 64 counters in one gather
-          // (counters only grow during a run, so the first is still ready)
-          const uint32_t v = ld_relaxed(ready + ((long)(j <= kb_last ? j : kb_last) * Mb + mb) * kLine);
-          m = __builtin_amdgcn_ballot_w64((j <= kb_last) & ((int32_t)(v - target) >= 0));
-          // ~m == 0 (all 64 ready) must be taken apart: a count of trailing
-          // zeros of 0 is undefined, and the scalar find-first-one the
-          // compiler emits for it returns -1.
-          hi = ~m ? kb + (int)__builtin_ctzll(~m) - 1 : kb + 63;
-        } else if (lane == 0) {
-          __hip_atomic_fetch_or(err, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
-      }
-      if (lane == 0) *s_known = hi >= 0 ? hi : 0x7fffffff;
+      const int hi = poll(kb);
+      if ((threadIdx.x & 63) == 0) *s_known = hi >= 0 ? hi : 0x7fffffff;
     }
     __syncthreads();
     const int known = uniform(*s_known);

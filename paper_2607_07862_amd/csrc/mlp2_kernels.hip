@@ -209,7 +209,7 @@ __device__ __forceinline__ void gemm1_item(const Args& a, int id_in, uint32_t ep
         float v[NB][8];
 #pragma unroll
         for (int b = 0; b < NB; ++b) pair_values<T>(acc[b], tp, tm, v[b]);
-        store_z<NB, SN>(a, fp.row0 + 16 * tm, fp.col0 + 32 * tp, v, tile != a.drop_signal);
+        store_z<NB, SN>(a, fp.row(tm), fp.col(tp), v, tile != a.drop_signal);
       }
   } else {
     const bool last = arrive_split<T, NB>(a.part1, a.cnt1 + (long)tile * kLine, tile, a.S1, s,
@@ -288,7 +288,7 @@ __device__ __forceinline__ void gemm2_item(const Args& a, int p_in, uint32_t epo
         for (int tp = 0; tp < T::TN / 2; ++tp) {
           float v[8];
           pair_values<T>(acc[h], tp, tm, v);
-          store_y(a, fp.row0 + 16 * tm, fp.col0 + h * T::BN + 32 * tp, v);
+          store_y(a, fp.row(tm), fp.col(tp) + h * T::BN, v);
         }
   } else if (a.red2 > 0) {
     // The tile is summed by its reduction items: store the partial and count
@@ -581,6 +581,7 @@ template <int NS> struct TileFor<128, 128, NS, 8> { using type = Tile<128, 128, 
 template <int NS> struct TileFor<128, 64, NS, 8> { using type = Tile<128, 64, 4, 2, NS>; };
 template <int NS> struct TileFor<64, 256, NS, 8> { using type = Tile<64, 256, 2, 4, NS>; };
 template <int NS> struct TileFor<32, 256, NS, 8> { using type = Tile<32, 256, 1, 8, NS>; };
+template <> struct TileFor<256, 128, 2, 8> { using type = Tile<256, 128, 2, 4, 2>; };  // the quadrant tile
 template <int BM, int BN, int NS, int W, int BK, bool WNT = false>
 struct TileForK {
   using base = typename TileFor<BM, BN, NS, W>::type;
@@ -709,7 +710,7 @@ __device__ __forceinline__ void chain_item(const ChainArgs& c, int layer, int ti
 #pragma unroll
         for (int i = 0; i < 8; ++i) v[i] = gelu_tanh(v[i]);
       }
-      const int row = fp.row0 + 16 * tm, col = fp.col0 + 32 * tp;
+      const int row = fp.row(tm), col = fp.col(tp);
       if (!L.guard || row < a.M) *reinterpret_cast<u32x4*>(L.out + (long)row * L.N + col) = pack_bf16x8(v);
     }
   // Producer signal (one per tile and run): this tile's output rows are released.
