@@ -280,9 +280,18 @@ __device__ __forceinline__ int swz_b(int k) {
 // explicitly with s_waitcnt vmcnt.  M0 carries the LDS address: it is an
 // operand of the asm ("{m0}" constraint), so the compiler itself writes it and
 // knows the register holds that value, and never has a value of its own there.
-__device__ __forceinline__ void dma16(const void* base, uint32_t voff, uint32_t lds_addr) {
-  asm volatile("global_load_lds_dwordx4 %0, %1" ::"v"(voff), "s"(base), "{m0}"(lds_addr) : "memory");
-}
+// The base goes through a scalar move of the asm's own: a vector-memory
+// instruction must not read a scalar register within five wait states of a
+// vector instruction that wrote it (a spilled scalar comes back by
+// v_readlane), which the compiler keeps for its own instructions but not for
+// the ones in here; the move also stands between the write of M0 and its use.
+#define MLP2_DMA16(FLAGS)                                                                              \
+  const void* b;                                                                                       \
+  asm volatile("s_mov_b64 %0, %2\n\tglobal_load_lds_dwordx4 %1, %0" FLAGS                              \
+               : "=&s"(b)                                                                              \
+               : "v"(voff), "s"(base), "{m0}"(lds_addr)                                                \
+               : "memory")
+__device__ __forceinline__ void dma16(const void* base, uint32_t voff, uint32_t lds_addr) { MLP2_DMA16(""); }
 
 // The same load at device scope (sc1, the scope bit of the compiler's own
 // agent-scope atomic loads): it reads the device's point of coherence rather
@@ -290,12 +299,13 @@ __device__ __forceinline__ void dma16(const void* base, uint32_t voff, uint32_t 
 // read the intermediate this way, since no release and acquire order it.
 // The same load with the non-temporal hint (a streamed operand read once).
 __device__ __forceinline__ void dma16_nt(const void* base, uint32_t voff, uint32_t lds_addr) {
-  asm volatile("global_load_lds_dwordx4 %0, %1 nt" ::"v"(voff), "s"(base), "{m0}"(lds_addr) : "memory");
+  MLP2_DMA16(" nt");
 }
 
 __device__ __forceinline__ void dma16_coherent(const void* base, uint32_t voff, uint32_t lds_addr) {
-  asm volatile("global_load_lds_dwordx4 %0, %1 sc1" ::"v"(voff), "s"(base), "{m0}"(lds_addr) : "memory");
+  MLP2_DMA16(" sc1");
 }
+#undef MLP2_DMA16
 
 // ------------------------------------------------------------------ sentinel synchronisation
 //
@@ -331,6 +341,20 @@ __device__ __forceinline__ void store_coherent16(uint16_t* p, u32x4 v) {
   uint64_t* q = reinterpret_cast<uint64_t*>(p);
   __hip_atomic_store(q, (uint64_t)v[0] | ((uint64_t)v[1] << 32), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   __hip_atomic_store(q + 1, (uint64_t)v[2] | ((uint64_t)v[3] << 32), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// 16 bytes stored through to the device's point of coherence (the sc1 bit of
+// the compiler's own agent-scope atomic stores): once the store is
+// acknowledged (vmcnt), every XCD can read it.  Data published inside a
+// launch (Z tiles, split-K partials) is stored this way, so publishing needs
+// only that wait and a relaxed atomic.  An agent-scope release instead writes
+// back the XCD's whole L2, once per work-group and item, in turn: at 32 rows
+// and less that was a third to half of the run (figures at release_add).
+// `base` is the same in every lane; `off` is in bytes, below 4 GiB.
+__device__ __forceinline__ void store_through16(void* base, uint32_t off, u32x4 v) {
+  constexpr int kSc1 = 16;
+  const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(base, 0, -1, 0x00027000);
+  __builtin_amdgcn_raw_buffer_store_b128(v, rsrc, (int)off, 0, kSc1);
 }
 
 // Wait until at most n of this wave's vector-memory operations are outstanding.
@@ -999,15 +1023,15 @@ struct Partial {
 
 template <class T, int NB>
 __device__ __forceinline__ void store_partial(float* base, long tile, int S, int s, const f32x4 (&acc)[NB][T::TN][T::TM]) {
-  f32x4* p = reinterpret_cast<f32x4*>(base) + Partial<T, NB>::block_index(tile, S, s, threadIdx.x >> 6, 0, 0, 0) +
-             (threadIdx.x & 63);
+  float* item = base + Partial<T, NB>::block_index(tile, S, s, 0, 0, 0, 0) * 4;
+  const uint32_t off = ((threadIdx.x >> 6) * Partial<T, NB>::PER_WAVE * 64 + (threadIdx.x & 63)) * 16;
   int i = 0;
 #pragma unroll
   for (int b = 0; b < NB; ++b)
 #pragma unroll
     for (int tn = 0; tn < T::TN; ++tn)
 #pragma unroll
-      for (int tm = 0; tm < T::TM; ++tm, ++i) p[i * 64] = acc[b][tn][tm];
+      for (int tm = 0; tm < T::TM; ++tm, ++i) store_through16(item, off + i * 1024, __builtin_bit_cast(u32x4, acc[b][tn][tm]));
 }
 
 // A reduction unit: wave w's blocks (2 tp, tm) and (2 tp + 1, tm).
@@ -1032,7 +1056,7 @@ struct Unit {
 // produces).  G units at a time and R parts per round keep 2*G*NB*R loads of
 // one wave in flight together; slots past the last part load part S - 1
 // again (in bounds) and are not added.
-template <class T, int NB, int G>
+template <class T, int NB, int G, int R>
 __device__ __forceinline__ void reduce_units(const float* base, long tile, int S, const Unit<T> (&ug)[G], int lane,
                                              float (&v)[G][NB][8]) {
   const f32x4* p = reinterpret_cast<const f32x4*>(base);
@@ -1042,7 +1066,6 @@ __device__ __forceinline__ void reduce_units(const float* base, long tile, int S
     for (int b = 0; b < NB; ++b)
 #pragma unroll
       for (int i = 0; i < 8; ++i) v[g][b][i] = 0.f;
-  constexpr int R = 8;
   for (int s = 0; s < S; s += R) {
     f32x4 q[R][G][NB][2];
 #pragma unroll
@@ -1072,32 +1095,48 @@ __device__ __forceinline__ void reduce_units(const float* base, long tile, int S
   }
 }
 
-// Release-increment of a counter after every wave's stores are complete
-// (used for split-K arrivals and for the producer's ready signal).
-__device__ __forceinline__ void release_add(uint32_t* cnt) {
-  wait_all_mem();
-  __syncthreads();
-  if (threadIdx.x == 0) __hip_atomic_fetch_add(cnt, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+// The parts a round loads: no more than the tile has, up to 8 (two parts in
+// rounds of eight read part 1 seven times: 2048 x 4096 x 14336, whose last
+// parts sum 512 KB a tile in the workqueue mode, 433 -> 390 us).  `f` is
+// called with the count as a constant.
+template <class F>
+__device__ __forceinline__ void with_round(int S, F&& f) {
+  if (S <= 2) f(int_constant<2>());
+  else if (S <= 4) f(int_constant<4>());
+  else f(int_constant<8>());
 }
 
-// A split-K part's arrival: store the partial, then one agent-scope release
-// increment of the tile's counter (after every wave's stores are complete).
+// Increment of a counter after every wave's stores through to the point of
+// coherence are acknowledged (used for split-K arrivals and for the producer's
+// ready signal): the stores are visible to the device before the count is.
+// Against an agent-scope release per increment and acquire-release exits
+// (pipelined mode): 1 x 4096 x 14336 gated 109 -> 82 us, 32 x 8192 x 3584
+// 51 -> 40, 128 x 4096 x 14336 92 -> 77, 64 x 512 x 2048 14.1 -> 12.1, a
+// chain of four 8192 x 8192 at 128 rows 222 -> 195.
+__device__ __forceinline__ void release_add(uint32_t* cnt) {
+  wait_vm<0>();
+  __syncthreads();
+  if (threadIdx.x == 0) __hip_atomic_fetch_add(cnt, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// A split-K part's arrival: store the partial, then one increment of the
+// tile's counter (after every wave's stores are acknowledged).
 // Returns true (uniformly) on the part that arrives last in this run, i.e.
 // that reads `target - 1`; that part then reads the others' partials after a
 // barrier and a work-group-scope acquire.  No agent-scope acquire is needed,
 // for the reason given for Z with the ready waits below: each tile's
 // partials (whole 1 KB runs, never sharing a line with another tile's) are
 // read once per launch, only by the completing part, after every part has
-// released them.
+// stored them through.
 template <class T, int NB>
 __device__ __forceinline__ bool arrive_split(float* part, uint32_t* cnt, long tile, int S, int s, uint32_t target,
                                              const f32x4 (&acc)[NB][T::TN][T::TM], int* s_slot, TraceAcc& tr) {
   store_partial<T, NB>(part, tile, S, s, acc);
-  wait_all_mem();
+  wait_vm<0>();
   __syncthreads();
   if constexpr (kTrace) tr.t_rel = trace_now();
   if (threadIdx.x == 0) {
-    const uint32_t old = __hip_atomic_fetch_add(cnt, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+    const uint32_t old = __hip_atomic_fetch_add(cnt, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     *s_slot = old == target - 1u;
   }
   __syncthreads();
@@ -1175,8 +1214,8 @@ struct NoClaim {
 // ------------------------------------------------------------------ ready flags
 
 // Producer side (Sec. III-A: the producer fences its output, then signals):
-// every wave's Z stores are complete, then one lane performs an agent-scope
-// release increment of the tile's ready counter.
+// every wave's Z stores are through to the point of coherence, then one lane
+// increments the tile's ready counter.
 __device__ __forceinline__ void signal_ready(uint32_t* flag) { release_add(flag); }
 
 // Consumer side: before loading Z columns [k, k + span) of row block mb (one
@@ -1194,8 +1233,8 @@ __device__ __forceinline__ void signal_ready(uint32_t* flag) { release_add(flag)
 // through LDS and a work-group barrier.  Every call is made by all waves with
 // the same k.
 //
-// Visibility of Z.  The producer's agent-scope release writes its Z lines
-// back from its XCD's L2 before the counter moves.  The consumer needs no
+// Visibility of Z.  The producer's Z lines are stored through its XCD's L2,
+// and acknowledged, before the counter moves.  The consumer needs no
 // agent-scope acquire (on this chip an invalidation of its XCD's whole L2,
 // which throws away the lines every other work-group of the XCD is
 // streaming, and measured several percent of a run where consumers wait
@@ -1316,19 +1355,18 @@ struct ReadyWait {
 
 __device__ __forceinline__ uint32_t queue_tag(uint32_t wq_epoch) { return ((wq_epoch + 1u) & 0xffu) << 24; }
 
-// Producer side: every wave's Z stores of the tile are complete, then wave 0
-// increments the scoreboard of each unit that reads the tile, one unit per
-// lane (agent-scope release: the tile's Z lines are written back before the
-// count moves).  The units whose count this completes are pushed together:
+// Producer side: every wave's Z stores of the tile are through to the point of
+// coherence, then wave 0 increments the scoreboard of each unit that reads the
+// tile, one unit per lane.  The units whose count this completes are pushed together:
 // lane 0 reserves as many queue slots as the ballot has bits with one atomic
 // (a tile that completes a whole split's units would otherwise pay one
 // round trip per unit, one after the other), and each completing lane
-// publishes its unit in its slot with a release store.  The queue has one spare slot
+// publishes its unit in its slot.  The queue has one spare slot
 // past the run's unit count; a reservation beyond it (impossible: each unit
 // completes once per run) would land there, no consumer reads it, and the
 // unit's consumer would time out and report the error.
 __device__ __forceinline__ void push_ready(const Args& a, int tile, uint32_t wq_epoch) {
-  wait_all_mem();
+  wait_vm<0>();
   __syncthreads();
   if (uniform((int)(threadIdx.x >> 6)) == 0) {  // wave 0, as a scalar branch
     const int lane = threadIdx.x & 63;
@@ -1346,7 +1384,7 @@ __device__ __forceinline__ void push_ready(const Args& a, int tile, uint32_t wq_
         const int kbeg = s * a.kc2, kend = min(a.F, kbeg + a.kc2);
         const uint32_t n = (uint32_t)((kend - 1) / a.bn1 - kbeg / a.bn1 + 1);
         const uint32_t old =
-            __hip_atomic_fetch_add(a.board + (long)q * kLine, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_fetch_add(a.board + (long)q * kLine, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         complete = old + 1u == (wq_epoch + 1u) * n;
       }
       const uint64_t m = __builtin_amdgcn_ballot_w64(complete);
@@ -1359,7 +1397,7 @@ __device__ __forceinline__ void push_ready(const Args& a, int tile, uint32_t wq_
         if (complete) {
           const uint32_t below = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
           __hip_atomic_store(a.queue + min(base + below, (uint32_t)a.items2), queue_tag(wq_epoch) | (uint32_t)q,
-                             __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+                             __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
       }
     }
@@ -1372,8 +1410,8 @@ __device__ __forceinline__ void push_ready(const Args& a, int tile, uint32_t wq_
 // once another wait gave up, it latches CTRL_ERROR and returns no unit.
 // Returns the unit for every wave, or -1 once the run's units are all
 // claimed.  Z visibility follows the ready counters' argument: every
-// producer of the unit released its Z lines before its increment, the
-// completing increment precedes the release store of the entry, and no L2
+// producer of the unit stored its Z lines through before its increment, the
+// completing increment had returned before the entry was stored, and no L2
 // holds a Z line before a consumer has seen its producers complete.
 __device__ __forceinline__ int pop_ready(const Args& a, uint32_t wq_epoch, int* s_bcast) {
   if (uniform((int)(threadIdx.x >> 6)) == 0) {  // wave 0, as a scalar branch

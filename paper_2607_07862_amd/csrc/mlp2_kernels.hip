@@ -27,7 +27,9 @@ namespace mlp2 {
 
 // GEMM1 epilogue for one lane: activation in fp32 on the 8 consecutive values
 // of row `row` from column `col`, round to bf16, one 16-byte store into Z.
-template <int NB, bool SN = false>
+// PUB: published inside the launch (stored through); the GEMM1 kernel's Z is
+// read by the next kernel only.
+template <int NB, bool SN = false, bool PUB = true>
 __device__ __forceinline__ void store_z(const Args& a, long row, int col, const float (&v)[NB][8], bool keep = true) {
   float z[8];
   if constexpr (NB == 2) {
@@ -49,6 +51,8 @@ __device__ __forceinline__ void store_z(const Args& a, long row, int col, const 
     if (keep) store_coherent16(a.Z + row * a.F + col, packed);  // !keep: a dropped tile (failure injection)
     const u32x4 sent = {0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu};
     *reinterpret_cast<u32x4*>(a.Zr + row * a.F + col) = sent;
+  } else if constexpr (PUB) {
+    store_through16(a.Z, (uint32_t)((row * a.F + col) * 2), packed);
   } else {
     *reinterpret_cast<u32x4*>(a.Z + row * a.F + col) = packed;
   }
@@ -137,15 +141,17 @@ __device__ __forceinline__ void reduce_epilogue(const float* part, long tile, in
   constexpr int G = NB == 1 ? 2 : 1;
   static_assert(U % G == 0, "units per group");
   const int lane = threadIdx.x & 63;
-  for (int u0 = uniform((int)(threadIdx.x >> 6)) * G; u0 < U; u0 += T::NWAVES * G) {
-    Unit<T> ug[G];
+  with_round(S, [&](auto r) {
+    for (int u0 = uniform((int)(threadIdx.x >> 6)) * G; u0 < U; u0 += T::NWAVES * G) {
+      Unit<T> ug[G];
 #pragma unroll
-    for (int g = 0; g < G; ++g) ug[g] = Unit<T>(u0 + g);
-    float v[G][NB][8];
-    reduce_units<T, NB, G>(part, tile, S, ug, lane, v);
+      for (int g = 0; g < G; ++g) ug[g] = Unit<T>(u0 + g);
+      float v[G][NB][8];
+      reduce_units<T, NB, G, decltype(r)::value>(part, tile, S, ug, lane, v);
 #pragma unroll
-    for (int g = 0; g < G; ++g) epi(ug[g], lane, v[g]);
-  }
+      for (int g = 0; g < G; ++g) epi(ug[g], lane, v[g]);
+    }
+  });
 }
 
 // One slice of a tile's reduction (reduction items): the tile's units in
@@ -158,16 +164,18 @@ __device__ __forceinline__ void reduce_slice(const float* part, long tile, int S
   static_assert(U % G == 0, "units per group");
   const int per = U / G / slices;  // groups per slice (the plan makes `slices` divide U / G)
   const int lane = threadIdx.x & 63;
-  for (int grp = uniform((int)(threadIdx.x >> 6)); grp < per; grp += T::NWAVES) {
-    const int u0 = (slice * per + grp) * G;
-    Unit<T> ug[G];
+  with_round(S, [&](auto r) {
+    for (int grp = uniform((int)(threadIdx.x >> 6)); grp < per; grp += T::NWAVES) {
+      const int u0 = (slice * per + grp) * G;
+      Unit<T> ug[G];
 #pragma unroll
-    for (int g = 0; g < G; ++g) ug[g] = Unit<T>(u0 + g);
-    float v[G][NB][8];
-    reduce_units<T, NB, G>(part, tile, S, ug, lane, v);
+      for (int g = 0; g < G; ++g) ug[g] = Unit<T>(u0 + g);
+      float v[G][NB][8];
+      reduce_units<T, NB, G, decltype(r)::value>(part, tile, S, ug, lane, v);
 #pragma unroll
-    for (int g = 0; g < G; ++g) epi(ug[g], lane, v[g]);
-  }
+      for (int g = 0; g < G; ++g) epi(ug[g], lane, v[g]);
+    }
+  });
 }
 
 // ------------------------------------------------------------------ work items
@@ -180,7 +188,7 @@ __device__ __forceinline__ void reduce_slice(const float* part, long tile, int S
 
 // GEMM1 item id = tile * S1 + s, tile = nb * Mb + mb.  WQ: the completed
 // tile also feeds the workqueue's scoreboards (wq_epoch: workqueue runs so far).
-template <class T, int NB, bool WQ = false, bool SN = false>
+template <class T, int NB, bool WQ = false, bool SN = false, bool PUB = true>
 __device__ __forceinline__ void gemm1_item(const Args& a, int id_in, uint32_t epoch, char* lds, int* s_slot,
                                            Claim& next, int* s_next, TraceAcc& tr, uint32_t wq_epoch = 0) {
   const int id = uniform(id_in);
@@ -209,7 +217,7 @@ __device__ __forceinline__ void gemm1_item(const Args& a, int id_in, uint32_t ep
         float v[NB][8];
 #pragma unroll
         for (int b = 0; b < NB; ++b) pair_values<T>(acc[b], tp, tm, v[b]);
-        store_z<NB, SN>(a, fp.row(tm), fp.col(tp), v, tile != a.drop_signal);
+        store_z<NB, SN, PUB>(a, fp.row(tm), fp.col(tp), v, tile != a.drop_signal);
       }
   } else {
     const bool last = arrive_split<T, NB>(a.part1, a.cnt1 + (long)tile * kLine, tile, a.S1, s,
@@ -217,7 +225,7 @@ __device__ __forceinline__ void gemm1_item(const Args& a, int id_in, uint32_t ep
     next.park(s_next);
     if (!last) return;
     reduce_epilogue<T, NB>(a.part1, tile, a.S1, [&](const Unit<T>& u, int lane, const float (&v)[NB][8]) {
-      store_z<NB, SN>(a, u.row(m0, lane), u.col(n0, lane), v, tile != a.drop_signal);
+      store_z<NB, SN, PUB>(a, u.row(m0, lane), u.col(n0, lane), v, tile != a.drop_signal);
     });
   }
   if constexpr (SN) return;  // no fence and no flag: consumers check the data itself
@@ -227,7 +235,9 @@ __device__ __forceinline__ void gemm1_item(const Args& a, int id_in, uint32_t ep
     tr.t_rel = trace_now();
   }
   if (tile != a.drop_signal) {
-    signal_ready(a.ready + (long)tile * kLine);
+    if constexpr (PUB) signal_ready(a.ready + (long)tile * kLine);
+    else if (threadIdx.x == 0)  // keeps the counters' epoch; nobody waits in this launch
+      __hip_atomic_fetch_add(a.ready + (long)tile * kLine, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if constexpr (WQ) push_ready(a, tile, wq_epoch);
   }
   if constexpr (kTrace) tr.t_wait = trace_now();
@@ -372,7 +382,10 @@ __device__ __forceinline__ void reduce_item(const Args& a, int r_in, uint32_t ep
 // list count and, at the end of a run, advances the epoch.  Everything is
 // stream-ordered before the plan's next kernel.  Spreading the done counts
 // over the lists keeps the exit atomics, one per work-group, off a single
-// line.
+// line.  The atomics are relaxed: each work-group's claims have returned
+// before its exit count, and nothing reads the words that are reset here
+// before the next kernel.  (With acquire-release exits every leaving
+// work-group wrote back and invalidated the L2 under those still running.)
 __device__ __forceinline__ void finish_kernel(const Args& a, bool roles, uint32_t epoch, bool end_of_run,
                                               bool wq_run = false, uint32_t wq_epoch = 0, bool sn_run = false,
                                               uint32_t sn_epoch = 0) {
@@ -381,12 +394,12 @@ __device__ __forceinline__ void finish_kernel(const Args& a, bool roles, uint32_
     const ListPos lp = list_pos(a, roles);
     const int l = lp.i % lp.lists;
     const uint32_t in_list = (uint32_t)((lp.n - 1 - l) / lp.lists + 1);
-    const uint32_t old = __hip_atomic_fetch_add(a.ctrl + ctrl_done(lp.list), 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
+    const uint32_t old = __hip_atomic_fetch_add(a.ctrl + ctrl_done(lp.list), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (old == in_list - 1u) {
       __hip_atomic_store(a.ctrl + ctrl_ticket(lp.list), 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       __hip_atomic_store(a.ctrl + ctrl_done(lp.list), 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       const uint32_t lists_done =
-          __hip_atomic_fetch_add(a.ctrl + CTRL_DONE_ALL, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
+          __hip_atomic_fetch_add(a.ctrl + CTRL_DONE_ALL, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       const uint32_t all_lists = (uint32_t)(lp.role < 0 ? a.lists : a.lists + a.lists2);
       if (lists_done == all_lists - 1u) {
         __hip_atomic_store(a.ctrl + CTRL_DONE_ALL, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -394,7 +407,7 @@ __device__ __forceinline__ void finish_kernel(const Args& a, bool roles, uint32_
         __hip_atomic_store(a.ctrl + CTRL_QTAIL, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (wq_run) __hip_atomic_store(a.ctrl + CTRL_EPOCH_WQ, wq_epoch + 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (sn_run) __hip_atomic_store(a.ctrl + CTRL_EPOCH_SN, sn_epoch + 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (end_of_run) __hip_atomic_store(a.ctrl + CTRL_EPOCH, epoch + 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+        if (end_of_run) __hip_atomic_store(a.ctrl + CTRL_EPOCH, epoch + 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       }
     }
   }
@@ -522,7 +535,7 @@ __global__ __launch_bounds__(T1::THREADS, (min_blocks<T1, NB, T2, HV, PHASE>()))
         gemm1_item<T1, NB>(a, (int)e, epoch, lds, &s_slot, next, &s_item, tr);
     } else if constexpr (PHASE == PHASE_GEMM1 || PHASE == PHASE_WORKQUEUE) {
       e = uniform(a.order1[p]);
-      gemm1_item<T1, NB, PHASE == PHASE_WORKQUEUE>(a, (int)e, epoch, lds, &s_slot, next, &s_item, tr, wq_epoch);
+      gemm1_item<T1, NB, PHASE == PHASE_WORKQUEUE, false, PHASE != PHASE_GEMM1>(a, (int)e, epoch, lds, &s_slot, next, &s_item, tr, wq_epoch);
     } else {
       e = uniform(a.order2[p]);
       if (e & 0x40000000u)
@@ -700,6 +713,7 @@ __device__ __forceinline__ void chain_item(const ChainArgs& c, int layer, int ti
   if constexpr (kTrace) tr_mark_mainloop(tr);
   next.park(s_next);
   FragPos<T> fp(m0, n0);
+  const bool pub = c.wait && L.ready_out;  // read inside this launch
 #pragma unroll
   for (int tm = 0; tm < T::TM; ++tm)
 #pragma unroll
@@ -711,9 +725,11 @@ __device__ __forceinline__ void chain_item(const ChainArgs& c, int layer, int ti
         for (int i = 0; i < 8; ++i) v[i] = gelu_tanh(v[i]);
       }
       const int row = fp.row(tm), col = fp.col(tp);
-      if (!L.guard || row < a.M) *reinterpret_cast<u32x4*>(L.out + (long)row * L.N + col) = pack_bf16x8(v);
+      const long at = (long)row * L.N + col;
+      if (pub) store_through16(L.out, (uint32_t)(at * 2), pack_bf16x8(v));
+      else if (!L.guard || row < a.M) *reinterpret_cast<u32x4*>(L.out + at) = pack_bf16x8(v);
     }
-  // Producer signal (one per tile and run): this tile's output rows are released.
+  // Producer signal (one per tile and run): this tile's output rows are stored through.
   if (L.ready_out) signal_ready(L.ready_out + (long)tile * kLine);
 }
 

@@ -197,3 +197,21 @@ def test_every_kernel_keeps_barriers_in_uniform_control_flow(asm):
         if v:
             problems[name] = v[:5]
     assert not problems, problems
+
+
+def dma_base_hazards(body):
+    """Direct-to-LDS loads (inline asm, so the compiler inserts no wait states)
+    whose base the instruction before them has not just moved: a vector-memory
+    instruction must not read a scalar register within five wait states of a
+    vector instruction writing it."""
+    lines = [l.split(";")[0].strip() for l in body.splitlines()]
+    lines = [l for l in lines if l and not l.startswith(".") and not l.startswith("#")]
+    return [l for prev, l in zip([""] + lines, lines)
+            if (m := re.match(r"global_load_lds_\w+ v\d+, (s\[\d+:\d+\])", l)) and not prev.startswith(f"s_mov_b64 {m.group(1)},")]
+
+
+def test_direct_to_lds_loads_read_a_base_moved_by_a_scalar_instruction(asm):
+    ks = kernels(asm)
+    assert any("global_load_lds" in b for b in ks.values())
+    problems = {n: dma_base_hazards(b)[:3] for n, b in ks.items() if dma_base_hazards(b)}
+    assert not problems, problems
