@@ -288,8 +288,10 @@ int mlp2_trace_attach(mlp2_plan_t plan, void* buffer, int records_per_group);
  * device array of 64 MiB that the library holds on each GPU it runs on until
  * the process ends.  Arguments and layouts as mlp2_plan / mlp2_run (device
  * pointers, row-major bf16, 16-byte aligned; the caller owns X, W1, W2, Y).
- * Returns MLP2_OK once enqueued; MLP2_ERR_UNSUPPORTED when the plan's
- * workspace exceeds the 64 MiB (e.g. the 70B gated MLP at 256 rows or a
+ * Where that plan's workspace exceeds the 64 MiB, tiles and splits that need
+ * less take its place (the sums over K then round differently).
+ * Returns MLP2_OK once enqueued; MLP2_ERR_UNSUPPORTED when that
+ * exceeds the 64 MiB too (e.g. the 70B gated MLP at 256 rows or a
  * prefill batch: use mlp2_plan for those), and the codes of mlp2_plan and
  * mlp2_run otherwise; mlp2_last_error() records the code.  Every call on a
  * device shares that device's array and starts by clearing its counters (a

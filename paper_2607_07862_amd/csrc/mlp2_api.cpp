@@ -283,6 +283,140 @@ void build_merged(const mlp2_plan_s* p, const std::vector<uint32_t>& order1, con
   for (const Key& k : keys) out.push_back(k.kind ? (0x80000000u | k.id) : k.id);
 }
 
+// Estimated time in us of one GEMM of `tiles` tiles and depth K, for the choice
+// between tile shapes beyond 256 rows: rounds of items over the launch's
+// work-group slots (a partial last round counts half and its share, since the
+// other GEMM's items fill part of it) times the stages of an item, and the
+// split-K partials' way out and back at 3.5 TB/s.  A 64-deep stage takes
+// `one_us` on a CU of its own, `full_us` when every slot is taken.
+double gemm_us(int64_t tiles, int64_t K, int slots, double tile_elems, double one_us, double full_us, int cus) {
+  int kc = 0;
+  const int S = choose_split(K, (int)std::min<int64_t>(tiles, 1 << 30), slots, 256, mlp2::kBK, &kc);
+  const double items = (double)tiles * S, r = items / slots, frac = r - (int64_t)r;
+  const double rounds = r <= 1 ? 1 : (int64_t)r + (frac < 0.05 ? frac : 0.5 + 0.5 * frac);
+  const double share = slots > cus ? std::min(1.0, std::max(0.0, items / cus - 1)) : 0;
+  return rounds * (kc / 64) * (one_us + (full_us - one_us) * share) + (S > 1 ? 8.0 * S * tiles * tile_elems / 3.5e6 : 0);
+}
+
+// Tiles of a plan that no tile tuning names.
+struct TileChoice {
+  int bm, bn1, bn2, ns, waves;
+};
+
+// The tiles for M > 256 rows: 256 x 256 quadrant tiles (1.40 us a stage), 128
+// x 128 tiles in two four-wave work-groups per CU (0.70 us alone on the CU,
+// 1.08 beside the other), or 128 x 128 tiles with a deep ring, one work-group
+// per CU (0.65 us; SwiGLU 0.70), whichever gemm_us finds fastest.  Measured
+// us, in that order, GELU:
+//   4096 x 14336, 300 / 512 / 777 / 2048 rows: 140 / 142 / 201 / 376, 138 /
+//     145 / 251 / 468, 156 / 166 / - / -
+//   4096 x 4096, 300 / 512 / 777 rows: two per CU 65 / 67 / 90, one 53 / 59 / 80
+//   2048 x 5632, 300 / 1000 rows: two per CU 51 / 64, one 46 / 76
+//   2112 x 5440, 777 / 1536 / 2048 rows: 88 / 94 / 105, 60 / 81 / 106
+// SwiGLU, quadrant and two per CU: 4096 x 14336, 300 / 512 / 2048 rows: 159 /
+// 161 / 558 and 186 / 206 / 683; 2112 x 5440, 512 / 777 / 2048 rows: 75 / 90 /
+// 149 and 56 / 87 / 170.  The estimates are within 20 % of these and their
+// order is right but for pairs within 5 % of each other.
+TileChoice many_row_tiles(int64_t M, int64_t H, int64_t F, int nb, int cus) {
+  const struct {
+    TileChoice t;
+    int per_cu;
+    double one_us, full_us;
+  } cand[] = {{{256, 256 / nb, 256, 2, 8}, 1, 1.40, 1.40},
+              {{128, 128 / nb, 128, 2, 4}, 2, 0.70, 1.08},
+              {{128, 128 / nb, 128, 4, nb == 1 ? 8 : 4}, 1, nb == 1 ? 0.65 : 0.70, 0}};
+  TileChoice best{};
+  double best_us = 0;
+  for (const auto& c : cand) {
+    const int64_t mb = ceil_div(M, c.t.bm);
+    // Z below 4 GiB with its padding
+    if (c.t.bm > 128 && (uint64_t)mb * c.t.bm * F * 2 >= (uint64_t)1 << 32) continue;
+    // a ring of four stages has nothing to run ahead of in items no longer than it
+    int kc1 = 0, kc2 = 0;
+    choose_split(H, (int)(mb * ceil_div(F, c.t.bn1)), c.per_cu * cus, 256, mlp2::kBK, &kc1);
+    choose_split(F, (int)(mb * ceil_div(H, c.t.bn2)), c.per_cu * cus, 256, mlp2::kBK, &kc2);
+    if (c.t.ns == 4 && std::max(kc1, kc2) <= 4 * mlp2::kBK) continue;
+    const double us = gemm_us(mb * ceil_div(F, c.t.bn1), H, c.per_cu * cus, (double)c.t.bm * c.t.bn1 * nb, c.one_us, c.full_us, cus) +
+                      gemm_us(mb * ceil_div(H, c.t.bn2), F, c.per_cu * cus, (double)c.t.bm * c.t.bn2, c.one_us, c.full_us, cus);
+    if (best_us == 0 || us < best_us) {
+      best = c.t;
+      best_us = us;
+    }
+  }
+  return best;
+}
+
+// Up to 256 rows the plan streams weights: few row blocks, so each weight byte
+// is read once or twice, and one item per CU (split-K makes them: more share a
+// CU's loads and cost more partials, 1 x 4096 x 14336 gated 73.6 us with 256
+// GEMM2 items, 81.8 with 576).  Narrow tiles for the short streams, whose
+// items would not fill the CUs otherwise; wide ones for the long, where they
+// halve the activation bytes per weight byte.  Measured us, pipelined, GELU:
+//   32 rows, bn2 64 / 128: 512 x 1472 12.9 / 14.3, 2048 x 5632 21.1 / 21.9,
+//     6144 x 1280 19.0 / 20.3, 4096 x 4096 23.4 / 22.1, 8192 x 3584 40.6 /
+//     33.5, 4096 x 14336 68.1 / 53.3
+//   64 rows, 64 / 128 columns: 2048 x 5632 23.3 / 28.9, 4096 x 4096 26.9 /
+//     29.8, 8192 x 3584 47.9 / 42.7, 4096 x 14336 79.7 / 58.6
+//   128 rows, 64 / 128 (eight waves): 2048 x 5632 28.5 / 34.2, 4096 x 4096
+//     30.6 / 37.0, 8192 x 3584 50.2 / 49.8, 4096 x 14336 76.8 / 68.5
+//   224 rows, 128 x 128 over eight waves / 256 x 128: 2048 x 5632 36.2 / 49.6,
+//     8192 x 3584 62.5 / 74.1, 4096 x 14336 93.8 / 95.7
+// and SwiGLU:
+//   128 rows, 64 x 64 and 64 x 128 tiles / 128-row ones: 2048 x 5632 31.0 /
+//     34.2, 6144 x 1280 31.1 / 37.3, 4096 x 4096 49.5 / 46.9, 4096 x 14336 115 / 88
+//   224 rows, 128-row tiles / quadrant tiles: 2048 x 5632 40.1 / 63.5, 8192 x
+//     3584 89 / 109, 4096 x 14336 137 / 117
+TileChoice choose_tiles(int64_t M, int64_t H, int64_t F, int nb, int cus) {
+  // items that 128-column tiles of an N-wide GEMM give with K ranges of 768
+  auto fill = [](int64_t N, int64_t K) { return ceil_div(N, 128) * std::max<int64_t>(1, K / 768); };
+  const bool wide = nb == 1 && fill(F, H) >= 192 && fill(H, F) >= 192;
+  if (M <= 32) return {32, 64, nb == 1 && fill(H, F) >= 128 ? 128 : 64, 4, 4};
+  if (M <= 64) {
+    if (wide) return {64, 128, 128, 4, 4};
+    // Too few 64-row tiles for a quarter of the CUs: 32-row tiles (64 x 512 x 2048: 14.7 -> 12.2 us).
+    return {ceil_div(F, 64) * std::max<int64_t>(1, H / 768) < cus / 4 ? 32 : 64, 64, 64, 4, 4};
+  }
+  if (M <= 128) {
+    if (nb == 1) return wide ? TileChoice{128, 128, 128, 4, 8} : TileChoice{128, 64, 64, 4, 4};
+    return {3 * H * F < (int64_t)80 << 20 ? 64 : 128, 64, 128, 4, 4};
+  }
+  if (M <= 256) {
+    if (nb == 1) return {128, 128, 128, 4, 8};
+    // (the smallest products keep the tiles that the parity tests pin)
+    if (H * F >= (int64_t)2 << 20 && H * F < (int64_t)40 << 20) return {128, 64, 128, 4, 4};
+    // 128 columns of each of Wg and Wu per tile, GEMM2 as two 128-column
+    // halves: half the activation bytes per weight byte of 64-column tiles
+    // (70B gated MLP, 256 rows: 600 -> 410 us with a plain mainloop).
+    if (F % 128 == 0 && H % 256 == 0) return {256, 128, 256, 2, 8};
+    return {256, 64, 128, 3, 4};
+  }
+  return many_row_tiles(M, H, F, nb, cus);
+}
+
+// The same with part of the tile, the splits or the grid named in the tuning:
+// preferences that the named fields replace, and the shallowest K range of a
+// split-K part.  (Also what mlp2_run_noalloc falls back to: fewer partials.)
+TileChoice tuned_tiles(int64_t M, int64_t H, int64_t F, int nb, int cus, int* min_k1, int* min_k2) {
+  *min_k1 = *min_k2 = 256;
+  if (M <= 32) {
+    *min_k1 = 2048;
+    *min_k2 = 1536;
+    return {32, F % 128 == 0 ? 128 : 64, 128, 4, 4};
+  }
+  if (M <= 64) {
+    const bool few = (int64_t)ceil_div(M, 64) * (F / 64) < cus / 4;
+    *min_k1 = *min_k2 = few ? 512 : 1024;
+    return {few ? 32 : 64, 64, 64, 4, 4};
+  }
+  if (M <= 128) return {128, 64, 64, 4, 4};
+  if (M <= 256) {
+    if (nb == 2 && F % 128 == 0 && H % 256 == 0) return {256, 128, 256, 2, 8};
+    return {256, nb == 1 ? 128 : 64, 128, 3, 4};
+  }
+  if (nb == 1 && F % 256 == 0 && H % 256 == 0 && (int64_t)ceil_div(M, 256) * (F / 256) >= cus) return {256, 256, 256, 2, 8};
+  return {128, 128, 128, 2, 4};
+}
+
 bool is_gfx950(int dev) {
   hipDeviceProp_t prop;
   if (hipGetDeviceProperties(&prop, dev) != hipSuccess) return false;
@@ -469,60 +603,22 @@ namespace mlp2 {
 // Everything a single-launch plan fixes before it has memory: tiles, split-K
 // factors, grids, the stage split.  No allocation (occupancy queries only).
 int configure_plan(mlp2_plan_s* p, int64_t M, int64_t H, int64_t F, int act, const mlp2_tuning_t& tz, int dev,
-                   int num_cus) {
+                   int num_cus, bool small_ws) {
   const int nb = act == MLP2_ACT_SWIGLU ? 2 : 1;
   p->M = M; p->H = H; p->F = F; p->act = act; p->device = dev;
   p->num_cus = num_cus;
 
-  // ---- tile choice by regime (each row chosen by measurement on MI355X).
-  // Up to 256 rows the plan streams weights: one row block holds every row,
-  // so each weight byte is read once, and split-K makes enough items.  At 32
-  // and 64 rows the per-item costs (pipeline fill, epilogue, split-K arrival)
-  // weigh more than idle CUs, so both GEMMs keep their K ranges deep; at 64
-  // rows small tiles shorten the latency-bound critical path.  Beyond 256 rows (MFMA-bound): 128 x 128 tiles, two work-groups
-  // per CU.
-  int pref[6] = {0, 0, 0, 0, 4, 64};  // bm, bn1, bn2, ring depth, waves, stage depth
+  // ---- tile choice by regime (measured on MI355X).  Without a tile tuning
+  // the last column block may be narrower than the tile (its loads are
+  // clamped, its stores guarded): 777 x 2112 x 5440, whose widths are odd
+  // multiples of 64, 86 us with 64-column tiles, 60 us with 128.
+  const bool tuned = small_ws || tz.bm || tz.bn1 || tz.bn2 || tz.stages || tz.waves || tz.bk || tz.splitk1 || tz.splitk2 || tz.grid || tz.p1;
   int min_k1 = 256, min_k2 = 256;  // shallowest K range of one split-K part
-  if (M <= 32) {
-    // 128-column GEMM1 tiles: half the activation bytes per weight byte of
-    // 64-column ones (one 70B tensor-parallel shard, 32 x 8192 x 3584:
-    // 42.2 -> 39.4 us pipelined)
-    pref[0] = 32; pref[1] = F % 128 == 0 ? 128 : 64; pref[2] = 128; pref[3] = 4;
-    min_k1 = 2048;
-    min_k2 = 1536;
-  } else if (M <= 64) {
-    pref[0] = 64; pref[1] = 64; pref[2] = 64; pref[3] = 4;
-    min_k1 = min_k2 = 1024;
-    // Too few 64-row GEMM1 tiles for a quarter of the CUs: 32-row tiles and
-    // 512-deep K ranges double the items that run side by side (measured at
-    // 64 x 512 x 2048: 16.4 -> 14.2 us pipelined, 17.8 -> 16.4 sequential).
-    if ((int64_t)ceil_div(M, 64) * (F / 64) < p->num_cus / 4) {
-      pref[0] = 32;
-      min_k1 = min_k2 = 512;
-    }
-  } else if (M <= 128) {
-    pref[0] = 128; pref[1] = 64; pref[2] = 64; pref[3] = 4;
-  } else if (M <= 256) {
-    pref[0] = 256; pref[1] = nb == 1 ? 128 : 64; pref[2] = 128; pref[3] = 3;
-    // Gated: 128 columns of each of Wg and Wu per tile over eight waves, GEMM2
-    // as two 128-column halves (two-stage ring): half the activation bytes per
-    // weight byte of the four-wave 64-column tile (70B gated MLP, 256 rows:
-    // 600 -> 410 us pipelined).
-    if (nb == 2 && F % 128 == 0 && H % 256 == 0) {
-      pref[1] = 128; pref[2] = 256; pref[3] = 2; pref[4] = 8;
-    }
-  } else {
-    pref[0] = 128; pref[1] = 128; pref[2] = 128; pref[3] = 2;
-    // 256 x 256 tiles over eight waves (a quarter of the operand bytes per flop
-    // of 128 x 128) once they fill every CU: Llama-8B prefill 2048 rows
-    // 523 -> 450 us pipelined, 8192 x 8192 weights at 8192 rows 2074 -> 1726 us.
-    if (nb == 1 && F % 256 == 0 && H % 256 == 0 && (int64_t)ceil_div(M, 256) * (F / 256) >= p->num_cus) {
-      pref[0] = 256; pref[1] = 256; pref[2] = 256; pref[3] = 2; pref[4] = 8;
-    }
-  }
+  const TileChoice tc = tuned ? tuned_tiles(M, H, F, nb, num_cus, &min_k1, &min_k2) : choose_tiles(M, H, F, nb, num_cus);
+  const int pref[4] = {tc.bm, tc.bn1, tc.bn2, tc.ns};
+  const bool ragged = !tuned;
   // Fallbacks when the preferred tiles do not divide F / H or are not built.
-  const int w = pref[4];
-  const int bk = pref[5];
+  const int w = tc.waves;
   const int cand[][5] = {
       {pref[0], pref[1], pref[2], pref[3], w}, {pref[0], pref[1], 64, pref[3], w}, {pref[0], 64, 64, pref[3], w},
       {pref[0], pref[1], pref[2], 4, w},       {pref[0], pref[1], 64, 4, w},       {pref[0], 64, 64, 4, w},
@@ -537,27 +633,27 @@ int configure_plan(mlp2_plan_s* p, int64_t M, int64_t H, int64_t F, int act, con
   // 405 -> 390 us sequential; after a 1 GiB flush: 389 -> 393 us pipelined,
   // 405 -> 398 us sequential).  Where the weights fit, a warm run reads part
   // of them from that cache, and the hint loses it (decode 80 -> 101 us,
-  // prefill 430 -> 452 us): off.
-  const bool big_weights = (uint64_t)(nb + 1) * (uint64_t)H * (uint64_t)F * 2 > ((uint64_t)256 << 20);
+  // prefill 430 -> 452 us): off; and off past 256 rows, where every row block
+  // reads the weights again (gated 8192 x 28672 with 512 / 1024 / 2048 rows:
+  // 592 / 1120 / 2034 us with the hint, 585 / 1098 / 1995 without).
+  const bool big_weights = M <= 256 && (uint64_t)(nb + 1) * (uint64_t)H * (uint64_t)F * 2 > ((uint64_t)256 << 20);
   const int nt_first = tz.weights_nt == 1 || (tz.weights_nt == 0 && big_weights) ? 1 : 0;
   const int nt_last = tz.weights_nt == 1 ? 1 : 0;  // forced on: no fallback without it
   bool found = false;
-  // The preferred stage depth first; the fallbacks with 64-deep stages; with
-  // the hint where wanted and built, else without.
-  for (int pass = 0; pass < 2 && !found; ++pass) {
-    for (const auto& c : cand) {
-      for (int nt = nt_first; nt >= nt_last && !found; --nt) {
-        KernelConfig k{tz.bm ? tz.bm : c[0], tz.bn1 ? tz.bn1 : c[1], tz.bn2 ? tz.bn2 : c[2], nb,
-                       tz.stages ? tz.stages : c[3], tz.waves ? tz.waves : c[4], tz.bk ? tz.bk : pass ? 64 : bk, nt};
-        // 128-deep stages need every K range (H; F; the split-K parts) in whole stages
-        if (F % k.bn1 == 0 && H % k.bn2 == 0 && (k.bk < 128 || (H % k.bk == 0 && F % k.bk == 0)) &&
-            mlp2::config_supported(k)) {
-          p->kc = k;
-          found = true;
-        }
+  // With the hint where wanted and built, else without.
+  for (const auto& c : cand) {
+    for (int nt = nt_first; nt >= nt_last && !found; --nt) {
+      KernelConfig k{tz.bm ? tz.bm : c[0], tz.bn1 ? tz.bn1 : c[1], tz.bn2 ? tz.bn2 : c[2], nb,
+                     tz.stages ? tz.stages : c[3], tz.waves ? tz.waves : c[4], tz.bk ? tz.bk : 64, nt};
+      // a width named in the tuning must divide; a chosen one may leave a narrower last block
+      const bool fits = (F % k.bn1 == 0 || ragged) && (H % k.bn2 == 0 || ragged);
+      // 128-deep stages need every K range (H; F; the split-K parts) in whole stages
+      if (fits && (k.bk < 128 || (H % k.bk == 0 && F % k.bk == 0)) && mlp2::config_supported(k)) {
+        p->kc = k;
+        found = true;
       }
-      if (found) break;
     }
+    if (found) break;
   }
   if (!found) return MLP2_ERR_UNSUPPORTED;
   const int bm = p->kc.bm, bn1 = p->kc.bn1, bn2 = p->kc.bn2;
@@ -568,25 +664,34 @@ int configure_plan(mlp2_plan_s* p, int64_t M, int64_t H, int64_t F, int act, con
   const uint64_t lim = (uint64_t)1 << 32;
   if ((uint64_t)M * H * 2 >= lim || (uint64_t)p->Mb * bm * F * 2 >= lim || (uint64_t)H * F * 2 >= lim)
     return MLP2_ERR_UNSUPPORTED;
-  p->Nb1 = (int)(F / bn1);
-  p->Nb2 = (int)(H / bn2);
+  p->Nb1 = ceil_div(F, bn1);
+  p->Nb2 = ceil_div(H, bn2);
   int occ[5] = {0, 0, 0, 0, 0};
   for (int w = 0; w < 5; ++w) {
     if (mlp2::occupancy(p->kc, w, &occ[w]) != hipSuccess || occ[w] < 1) return MLP2_ERR_HIP;
   }
   const int tiles1 = p->Mb * p->Nb1, tiles2 = p->Mb * p->Nb2;
   const int gran = std::max(mlp2::kBK, p->kc.bk);  // split-K parts hold whole stages
+  // Items wanted: the launch's slots; for a streaming plan one per CU, with K
+  // ranges of at least 768, or 512 where that leaves most CUs idle (32 rows:
+  // 6144 x 1280 20.6 us with 512, 19.0 with 768; 512 x 1472 12.9 and 14.3).
+  const bool streams = !tuned && M <= 256;
+  const int want1 = (streams ? 1 : occ[0]) * p->num_cus, want2 = (streams ? 1 : occ[1]) * p->num_cus;
+  if (streams) {
+    min_k1 = tiles1 * std::max<int64_t>(1, H / 768) < p->num_cus / 4 ? 512 : 768;
+    min_k2 = tiles2 * std::max<int64_t>(1, F / 768) < p->num_cus / 4 ? 512 : 768;
+  }
   if (tz.splitk1) {
     p->kc1 = (int)align_up((size_t)ceil_div(H, tz.splitk1), gran);
     p->S1 = ceil_div(H, p->kc1);
   } else {
-    p->S1 = choose_split(H, tiles1, occ[0] * p->num_cus, min_k1, gran, &p->kc1);
+    p->S1 = choose_split(H, tiles1, want1, min_k1, gran, &p->kc1);
   }
   if (tz.splitk2) {
     p->kc2 = (int)align_up((size_t)ceil_div(F, tz.splitk2), gran);
     p->S2 = ceil_div(F, p->kc2);
   } else {
-    p->S2 = choose_split(F, tiles2, occ[1] * p->num_cus, min_k2, gran, &p->kc2);
+    p->S2 = choose_split(F, tiles2, want2, min_k2, gran, &p->kc2);
   }
   p->order = tz.order;
   p->lag = tz.lag;

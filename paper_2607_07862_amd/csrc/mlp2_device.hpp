@@ -379,8 +379,9 @@ __device__ __forceinline__ void wait_stages_behind(int after) {
 // ------------------------------------------------------------------ mainloop
 
 // acc[b][tn][tm] = sum over k in [kbeg, kend) of W_b[k][n] * A[m][k] for the
-// tile at (m0, n0).  A rows past `mlast` are clamped to `mlast` (their results
-// are never stored).  `wait(k)` runs, in every wave, before the activation
+// tile at (m0, n0[b]).  A rows past `mlast` are clamped to `mlast`, and
+// columns past the last 8 of W's `ldb` to those (the results of either are
+// never stored).  `wait(k)` runs, in every wave, before the activation
 // operand of the stage starting at k is requested (after its weight loads).
 //
 // Pipeline: stages k0, k0 + BK, ... are loaded NS - 1 ahead of use.  At
@@ -437,8 +438,8 @@ struct NoCheck {
 // The products of one output run in the same order as in the plain mainloop.
 template <class T, int NB, class Wait>
 __device__ __forceinline__ void mainloop_quad(const uint16_t* __restrict__ A, long lda, int m0, int mlast,
-                                              const uint16_t* const (&Bp)[NB], long ldb, int n0, int kbeg, int kend,
-                                              f32x4 (&acc)[NB][T::TN][T::TM], char* lds, Wait& wait, TraceAcc& tr) {
+                                              const uint16_t* const (&Bp)[NB], const int (&n0)[NB], long ldb, int kbeg,
+                                              int kend, f32x4 (&acc)[NB][T::TN][T::TM], char* lds, Wait& wait, TraceAcc& tr) {
   static_assert(T::QUAD && NB * T::BN == 256 && T::TM == 8 && NB * T::TN == 4 && T::NWAVES == 8, "quadrant tile");
   int tid = threadIdx.x;
   asm volatile("" : "+v"(tid));  // per-lane offsets are derived per call, as in the plain mainloop
@@ -461,7 +462,7 @@ __device__ __forceinline__ void mainloop_quad(const uint16_t* __restrict__ A, lo
 
   // Load sources: per-lane offsets from a per-stage uniform base.  A half: 128
   // rows of 128 bytes, 8 to a 1 KB piece; B half: 64 rows of 256 bytes, 4 to a piece.
-  uint32_t a_off[4], b_off[2];
+  uint32_t a_off[4], b_off[2][2];
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
     const int row = 8 * (wave + 8 * j) + lane / 8;
@@ -470,14 +471,15 @@ __device__ __forceinline__ void mainloop_quad(const uint16_t* __restrict__ A, lo
     a_off[j] = (uint32_t)(((long)gr * lda + 8 * ((lane & 7) ^ swz_a<64>(row))) * 2);
   }
 #pragma unroll
-  for (int j = 0; j < 2; ++j) {
-    const int row = 4 * (wave + 8 * j) + lane / 16;
-    b_off[j] = (uint32_t)(((long)row * ldb + 8 * ((lane & 15) ^ swz_b<128>(row))) * 2);
-  }
+  for (int h = 0; h < 2; ++h)
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const int row = 4 * (wave + 8 * j) + lane / 16;
+      const int col = (NB == 2 ? n0[h % NB] : n0[0] + 128 * h) + 8 * ((lane & 15) ^ swz_b<128>(row));
+      b_off[h][j] = (uint32_t)(((long)row * ldb + min(col, (int)ldb - 8)) * 2);
+    }
   const uint16_t* pa = A + kbeg;
-  const uint16_t* pb[2];
-  pb[0] = Bp[0] + (long)kbeg * ldb + n0;
-  pb[1] = NB == 2 ? Bp[NB - 1] + (long)kbeg * ldb + n0 : pb[0] + 128;
+  const uint16_t* pb[2] = {Bp[0] + (long)kbeg * ldb, Bp[NB - 1] + (long)kbeg * ldb};
 
   auto load_a = [&](int half, int st) {
     const uint32_t dst = lds_base + (uint32_t)(st & 1) * kStage + (uint32_t)half * kHalf + (uint32_t)wave * 1024u;
@@ -489,8 +491,8 @@ __device__ __forceinline__ void mainloop_quad(const uint16_t* __restrict__ A, lo
     const uint16_t* src = pb[half] + (long)st * 64 * ldb;
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
-      if constexpr (T::WNT) dma16_nt(src, b_off[j], uniform(dst + 8192u * j));
-      else dma16(src, b_off[j], uniform(dst + 8192u * j));
+      if constexpr (T::WNT) dma16_nt(src, b_off[half][j], uniform(dst + 8192u * j));
+      else dma16(src, b_off[half][j], uniform(dst + 8192u * j));
     }
   };
 
@@ -651,11 +653,11 @@ __device__ __forceinline__ void mainloop_quad(const uint16_t* __restrict__ A, lo
 
 template <class T, int NB, class Wait, class Check = NoCheck>
 __device__ __forceinline__ void mainloop(const uint16_t* __restrict__ A, long lda, int m0, int mlast,
-                                         const uint16_t* const (&Bp)[NB], long ldb, int n0, int kbeg, int kend,
-                                         f32x4 (&acc)[NB][T::TN][T::TM], char* lds, Wait& wait, TraceAcc& tr,
+                                         const uint16_t* const (&Bp)[NB], const int (&n0)[NB], long ldb, int kbeg,
+                                         int kend, f32x4 (&acc)[NB][T::TN][T::TM], char* lds, Wait& wait, TraceAcc& tr,
                                          Check check = Check()) {
   if constexpr (T::QUAD && NB * T::BN == 256 && is_same_type<Check, NoCheck>::value) {
-    mainloop_quad<T, NB>(A, lda, m0, mlast, Bp, ldb, n0, kbeg, kend, acc, lds, wait, tr);
+    mainloop_quad<T, NB>(A, lda, m0, mlast, Bp, n0, ldb, kbeg, kend, acc, lds, wait, tr);
     return;
   }
   // The thread index passes through an empty asm, so the compiler derives
@@ -697,14 +699,16 @@ __device__ __forceinline__ void mainloop(const uint16_t* __restrict__ A, long ld
   }
   constexpr int CPR = T::BN / 8;      // 16-byte chunks per weight row
   constexpr int RPC = 64 / CPR;       // weight rows per 1 KB chunk
-  uint32_t b_off[T::B_DMA];
+  uint32_t b_off[NB][T::B_DMA];
 #pragma unroll
-  for (int j = 0; j < T::B_DMA; ++j) {
-    const int ch = wave + T::NWAVES * j;
-    const int row = RPC * ch + lane / CPR;
-    const int lc = (lane % CPR) ^ swz_b<T::BN>(row);
-    b_off[j] = (uint32_t)(((long)row * ldb + n0 + 8 * lc) * 2);
-  }
+  for (int b = 0; b < NB; ++b)
+#pragma unroll
+    for (int j = 0; j < T::B_DMA; ++j) {
+      const int ch = wave + T::NWAVES * j;
+      const int row = RPC * ch + lane / CPR;
+      const int lc = (lane % CPR) ^ swz_b<T::BN>(row);
+      b_off[b][j] = (uint32_t)(((long)row * ldb + min(n0[b] + 8 * lc, (int)ldb - 8)) * 2);
+    }
 
   // A stage's loads: the activation rows first (measured on the gated GEMM1
   // operand stream without math, 256 activation rows and two 128-column
@@ -727,9 +731,9 @@ __device__ __forceinline__ void mainloop(const uint16_t* __restrict__ A, long ld
         for (int j = 0; j < T::B_DMA; ++j) {
           const uint32_t dst = uniform(sbase + (uint32_t)(T::A_BYTES + b * T::B_BYTES + (wave + T::NWAVES * j) * 1024));
           if constexpr (T::WNT)
-            dma16_nt(Bp[b], b_off[j] + (uint32_t)((long)k * ldb * 2), dst);
+            dma16_nt(Bp[b], b_off[b][j] + (uint32_t)((long)k * ldb * 2), dst);
           else
-            dma16(Bp[b], b_off[j] + (uint32_t)((long)k * ldb * 2), dst);
+            dma16(Bp[b], b_off[b][j] + (uint32_t)((long)k * ldb * 2), dst);
         }
     };
     auto activations = [&]() {

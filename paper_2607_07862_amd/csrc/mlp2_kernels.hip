@@ -44,6 +44,7 @@ __device__ __forceinline__ void store_z(const Args& a, long row, int col, const 
     }
   }
   const u32x4 packed = canonicalize_z(pack_bf16x8(z));  // never the sentinel pattern
+  if (col >= a.F) return;                               // the last column block may be wider than what is left
   if constexpr (SN) {
     // Sentinel mode: the piece goes straight to the device's point of
     // coherence, with no fence or flag after it; the same piece of the next
@@ -59,7 +60,7 @@ __device__ __forceinline__ void store_z(const Args& a, long row, int col, const 
 }
 
 __device__ __forceinline__ void store_y(const Args& a, int row, int col, const float (&v)[8]) {
-  if (row < a.M) *reinterpret_cast<u32x4*>(a.Y + (long)row * a.H + col) = pack_bf16x8(v);
+  if (row < a.M && col < a.H) *reinterpret_cast<u32x4*>(a.Y + (long)row * a.H + col) = pack_bf16x8(v);
 }
 
 // Claim lists.  Work-groups are placed on the XCDs round-robin by index, so
@@ -200,11 +201,15 @@ __device__ __forceinline__ void gemm1_item(const Args& a, int id_in, uint32_t ep
 
   f32x4 acc[NB][T::TN][T::TM];
   const uint16_t* Bp[NB];
-  Bp[0] = a.W1;
-  if constexpr (NB == 2) Bp[1] = a.W1 + (long)a.H * a.F;
+  int nb0[NB];
+#pragma unroll
+  for (int b = 0; b < NB; ++b) {
+    Bp[b] = a.W1 + b * (long)a.H * a.F;
+    nb0[b] = n0;
+  }
   NoWait nowait;  // a GEMM1 item never waits
   ClaimAtLastStage<NoWait> hook{nowait, &next, kend - T::BK};
-  mainloop<T, NB>(a.X, a.H, m0, a.M - 1, Bp, a.F, n0, kbeg, kend, acc, lds, hook, tr);
+  mainloop<T, NB>(a.X, a.H, m0, a.M - 1, Bp, nb0, a.F, kbeg, kend, acc, lds, hook, tr);
   if constexpr (kTrace) tr_mark_mainloop(tr);
 
   if (a.S1 == 1) {
@@ -264,8 +269,12 @@ __device__ __forceinline__ void gemm2_item(const Args& a, int p_in, uint32_t epo
 
   f32x4 acc[HV][T::TN][T::TM];
   const uint16_t* Bp[HV];
+  int nb0[HV];
 #pragma unroll
-  for (int h = 0; h < HV; ++h) Bp[h] = a.W2 + h * T::BN;
+  for (int h = 0; h < HV; ++h) {
+    Bp[h] = a.W2;
+    nb0[h] = n0 + h * T::BN;
+  }
   const int zlast = a.Mb * T::BM - 1;
   if constexpr (SN) {
     // Sentinel mode: no ready counters; each stage's Z pieces are loaded at
@@ -273,17 +282,17 @@ __device__ __forceinline__ void gemm2_item(const Args& a, int p_in, uint32_t epo
     NoWait nowait;
     ClaimAtLastStage<NoWait, C> hook{nowait, &next, kend - T::BK};
     SentinelCheck check{a.ctrl + CTRL_ERROR, a.spin_limit, &tr};
-    mainloop<T, HV>(a.Z, a.F, m0, zlast, Bp, a.H, n0, kbeg, kend, acc, lds, hook, tr, check);
+    mainloop<T, HV>(a.Z, a.F, m0, zlast, Bp, nb0, a.H, kbeg, kend, acc, lds, hook, tr, check);
   } else if constexpr (WAIT) {
     // ready counters advance once per run of every mode but the sentinel mode
     ReadyWait w{a.ready, a.ctrl + CTRL_ERROR, mb, a.Mb, a.bn1, (kend - 1) / a.bn1, ready_runs + 1u, a.spin_limit,
                 s_slot, 0, &tr, T::BK};
     ClaimAtLastStage<ReadyWait, C> hook{w, &next, kend - T::BK};
-    mainloop<T, HV>(a.Z, a.F, m0, zlast, Bp, a.H, n0, kbeg, kend, acc, lds, hook, tr);
+    mainloop<T, HV>(a.Z, a.F, m0, zlast, Bp, nb0, a.H, kbeg, kend, acc, lds, hook, tr);
   } else {
     NoWait nowait;
     ClaimAtLastStage<NoWait, C> hook{nowait, &next, kend - T::BK};
-    mainloop<T, HV>(a.Z, a.F, m0, zlast, Bp, a.H, n0, kbeg, kend, acc, lds, hook, tr);
+    mainloop<T, HV>(a.Z, a.F, m0, zlast, Bp, nb0, a.H, kbeg, kend, acc, lds, hook, tr);
   }
   if constexpr (kTrace) tr_mark_mainloop(tr);
 
@@ -700,15 +709,16 @@ __device__ __forceinline__ void chain_item(const ChainArgs& c, int layer, int ti
   const int K = L.K;
   f32x4 acc[1][T::TN][T::TM];
   const uint16_t* Bp[1] = {L.W};
+  const int nb0[1] = {n0};
   if (c.wait && L.ready_in) {
     ReadyWait w{L.ready_in, a.ctrl + CTRL_ERROR, mb, a.Mb, T::BN, (K - 1) / T::BN, epoch + 1u, a.spin_limit, s_slot,
                 0, &tr, T::BK};
     ClaimAtLastStage<ReadyWait> hook{w, &next, K - T::BK};
-    mainloop<T, 1>(L.A, K, m0, L.alast, Bp, L.N, n0, 0, K, acc, lds, hook, tr);
+    mainloop<T, 1>(L.A, K, m0, L.alast, Bp, nb0, L.N, 0, K, acc, lds, hook, tr);
   } else {
     NoWait nowait;
     ClaimAtLastStage<NoWait> hook{nowait, &next, K - T::BK};
-    mainloop<T, 1>(L.A, K, m0, L.alast, Bp, L.N, n0, 0, K, acc, lds, hook, tr);
+    mainloop<T, 1>(L.A, K, m0, L.alast, Bp, nb0, L.N, 0, K, acc, lds, hook, tr);
   }
   if constexpr (kTrace) tr_mark_mainloop(tr);
   next.park(s_next);

@@ -63,8 +63,9 @@ struct PlanLayout {
       ordp_off, zs_off, zs_bytes, bytes;
 };
 
+// small_ws: prefer the tiles and splits that need less workspace.
 int configure_plan(mlp2_plan_s* p, int64_t M, int64_t H, int64_t F, int act, const mlp2_tuning_t& tz, int dev,
-                   int num_cus);
+                   int num_cus, bool small_ws = false);
 // with_zs: room for the sentinel mode's two intermediates (zs_bytes, else 0).
 size_t plan_layout(const mlp2_plan_s* p, bool own_z, PlanLayout* L, bool with_zs = true);
 void bind_plan(mlp2_plan_s* p, char* base, const PlanLayout& L, uint16_t* z_ext);
