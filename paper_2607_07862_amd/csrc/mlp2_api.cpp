@@ -883,7 +883,7 @@ int launch_plan(const mlp2_plan_s* p, const void* X, const void* W1, const void*
   a.trace_cap = p->trace_cap;
   a.p1 = 0;
   a.lists2 = 0;
-  a.red2 = p->red2;  // the sequential GEMM2 kernel and the pipelined launch use reduction items
+  a.red2 = p->red2;  // all but the sentinel launch use reduction items
   a.items_red = p->items_red;
   a.Zs = p->Zs;
   a.zs_elems = (long)p->Mb * p->kc.bm * p->F;
@@ -930,8 +930,6 @@ int launch_plan(const mlp2_plan_s* p, const void* X, const void* W1, const void*
     a.first_static = statics(p->lead1, gridp);
     err = mlp2::launch_sentinel(p->kc, a, gridp, s);
   } else {
-    a.red2 = 0;  // workqueue units: the last part sums the tile (same order, same bits)
-    a.items_red = 0;
     a.lists = claim_lists(gridp);
     a.first_static = statics(p->items1, gridp);  // every ranked item is a GEMM1 item
     err = mlp2::launch_workqueue(p->kc, a, gridp, s);

@@ -1412,8 +1412,9 @@ __device__ __forceinline__ void push_ready(const Args& a, int tile, uint32_t wq_
 // at the same address, a scalar loop with uniform exits) until a producer of
 // this run has filled it, sleeping between polls; after spin_limit polls, or
 // once another wait gave up, it latches CTRL_ERROR and returns no unit.
-// Returns the unit for every wave, or -1 once the run's units are all
-// claimed.  Z visibility follows the ready counters' argument: every
+// Returns the unit for every wave; past the run's units, items2 + r for
+// reduction item r (nothing to wait for here: it waits for its tile's parts
+// itself); or -1 once all are claimed.  Z visibility follows the ready counters' argument: every
 // producer of the unit stored its Z lines through before its increment, the
 // completing increment had returned before the entry was stored, and no L2
 // holds a Z line before a consumer has seen its producers complete.
@@ -1442,6 +1443,8 @@ __device__ __forceinline__ int pop_ready(const Args& a, uint32_t wq_epoch, int* 
         }
         __builtin_amdgcn_s_sleep(2);
       }
+    } else if (h < (uint32_t)(a.items2 + a.items_red)) {
+      q = (int)h;
     }
     if (lane == 0) *s_bcast = q;
   }
