@@ -29,10 +29,10 @@ struct mlp2_chain_s {
   int act = 0;
   int device = -1;
   int num_cus = 0;
-  int tile = 0;                           // chain tile shape (index into kChainTiles)
-  int bt = 0;                             // its rows and columns
+  int tile = 0;                           // chain tile shape (index into kChainRows, kChainCols)
+  int bm = 0, bn = 0;                     // its rows and columns
   int Mb = 0;
-  int items[mlp2::kChainMaxLayers] = {};  // tiles per layer: Mb * D_l / bt
+  int items[mlp2::kChainMaxLayers] = {};  // tiles per layer: Mb * D_l / bn
   int total = 0;
   int grid = 0;
   uint32_t spin_limit = 1u << 20;
@@ -306,12 +306,15 @@ struct TileChoice {
 // The tiles for M > 256 rows: 256 x 256 quadrant tiles (1.40 us a stage), 128
 // x 128 tiles in two four-wave work-groups per CU (0.70 us alone on the CU,
 // 1.08 beside the other), or 128 x 128 tiles with a deep ring, one work-group
-// per CU (0.65 us; SwiGLU 0.70), whichever gemm_us finds fastest.  Measured
+// per CU (0.65 us; SwiGLU 0.70), or 256 x 128 pair tiles (0.90 us; not
+// SwiGLU), whichever gemm_us finds fastest.  Measured
 // us, in that order, GELU:
 //   4096 x 14336, 300 / 512 / 777 / 2048 rows: 140 / 142 / 201 / 376, 138 /
 //     145 / 251 / 468, 156 / 166 / - / -
-//   4096 x 4096, 300 / 512 / 777 rows: two per CU 65 / 67 / 90, one 53 / 59 / 80
-//   2048 x 5632, 300 / 1000 rows: two per CU 51 / 64, one 46 / 76
+//   4096 x 4096, 300 / 512 / 777 rows: two per CU 65 / 67 / 90, one 53 / 59 /
+//     80, pair - / 68 / 94
+//   2048 x 5632, 300 / 1000 rows: two per CU 51 / 64, one 46 / 76, pair - / 64
+//   8192 x 8192, 1024 rows: quadrant 251, pair 245
 //   2112 x 5440, 777 / 1536 / 2048 rows: 88 / 94 / 105, 60 / 81 / 106
 // SwiGLU, quadrant and two per CU: 4096 x 14336, 300 / 512 / 2048 rows: 159 /
 // 161 / 558 and 186 / 206 / 683; 2112 x 5440, 512 / 777 / 2048 rows: 75 / 90 /
@@ -324,10 +327,12 @@ TileChoice many_row_tiles(int64_t M, int64_t H, int64_t F, int nb, int cus) {
     double one_us, full_us;
   } cand[] = {{{256, 256 / nb, 256, 2, 8}, 1, 1.40, 1.40},
               {{128, 128 / nb, 128, 2, 4}, 2, 0.70, 1.08},
-              {{128, 128 / nb, 128, 4, nb == 1 ? 8 : 4}, 1, nb == 1 ? 0.65 : 0.70, 0}};
+              {{128, 128 / nb, 128, 4, nb == 1 ? 8 : 4}, 1, nb == 1 ? 0.65 : 0.70, 0},
+              {{256, 128, 128, 3, 8}, 1, 0.90, 0}};
   TileChoice best{};
   double best_us = 0;
   for (const auto& c : cand) {
+    if (c.t.ns == 3 && nb == 2) continue;  // the pair tile has one weight operand
     const int64_t mb = ceil_div(M, c.t.bm);
     // Z below 4 GiB with its padding
     if (c.t.bm > 128 && (uint64_t)mb * c.t.bm * F * 2 >= (uint64_t)1 << 32) continue;
@@ -1172,11 +1177,14 @@ extern "C" {
 
 namespace {
 
-// Chain tile (an index into kChainTiles): 256 x 256 over eight waves when
-// every layer's width is a multiple of 256 and the narrowest layer still
-// has a tile per CU; else 128 x 128, unless the narrowest layer would then
-// have fewer tiles than CUs: 64 x 64 (four times the items) for chains of
-// few rows.
+// Chain tile (an index into kChainRows): 256 x 256 when every layer's width is
+// a multiple of 256 and the narrowest layer still has a tile per CU; 256 x 128
+// when that layer has one of those for three quarters of the CUs; else 128 x
+// 128, unless the narrowest layer would then have fewer tiles than CUs: 64 x
+// 64 (four times the items) for chains of few rows.  Measured us, pipelined,
+// 128 x 128 / 256 x 128 / 256 x 256 tiles: four layers of 8192 with 700 / 1024
+// rows 457 / 428 / -, 536 / 487 / 568; four of 4096 with 1500 / 2048 rows
+// 240 / 223 / 307, 285 / 259 / 309; three of 2048 with 2000 rows 77 / 87 / 131.
 int chain_tile(int64_t M, int layers, const int64_t* dims, int cus) {
   int64_t narrowest = dims[1];
   bool wide = true;
@@ -1185,6 +1193,7 @@ int chain_tile(int64_t M, int layers, const int64_t* dims, int cus) {
     wide = wide && dims[l] % 256 == 0;
   }
   if (wide && (int64_t)ceil_div(M, 256) * (narrowest / 256) >= cus) return 2;
+  if ((int64_t)ceil_div(M, 256) * (narrowest / 128) >= cus * 3 / 4) return 3;
   return (int64_t)ceil_div(M, 128) * (narrowest / 128) < cus ? 1 : 0;
 }
 
@@ -1216,15 +1225,16 @@ mlp2_chain_s* make_chain(int64_t M, int layers, const int64_t* dims, int act, in
   p->M = M; p->L = layers; p->act = act; p->device = dev; p->num_cus = prop.multiProcessorCount;
   for (int l = 0; l <= layers; ++l) p->dims[l] = dims[l];
   p->tile = tile;
-  p->bt = mlp2::kChainTiles[tile];
-  p->Mb = ceil_div(M, p->bt);
+  p->bm = mlp2::kChainRows[tile];
+  p->bn = mlp2::kChainCols[tile];
+  p->Mb = ceil_div(M, p->bm);
   // 32-bit byte offsets of the direct-to-LDS loads: X, every intermediate
   // and every weight matrix stay below 4 GB.
   const uint64_t lim = (uint64_t)1 << 32;
   bool too_big = (uint64_t)M * dims[0] * 2 >= lim;
   for (int l = 0; l < layers; ++l) {
     too_big |= (uint64_t)dims[l] * dims[l + 1] * 2 >= lim;
-    if (l + 1 < layers) too_big |= (uint64_t)p->Mb * p->bt * dims[l + 1] * 2 >= lim;
+    if (l + 1 < layers) too_big |= (uint64_t)p->Mb * p->bm * dims[l + 1] * 2 >= lim;
   }
   if (too_big) {
     delete p;
@@ -1232,7 +1242,7 @@ mlp2_chain_s* make_chain(int64_t M, int layers, const int64_t* dims, int act, in
     return nullptr;
   }
   for (int l = 0; l < layers; ++l) {
-    p->items[l] = (int)(p->Mb * (dims[l + 1] / p->bt));
+    p->items[l] = (int)(p->Mb * (dims[l + 1] / p->bn));
     p->seq_off[l] = p->total;
     p->total += p->items[l];
   }
@@ -1240,7 +1250,7 @@ mlp2_chain_s* make_chain(int64_t M, int layers, const int64_t* dims, int act, in
   p->grid = std::min(occ * p->num_cus, p->total);
 
   // workspace: intermediates, then ready counters and control words (zeroed), then rank tables
-  const int64_t Mpad = (int64_t)p->Mb * p->bt;
+  const int64_t Mpad = (int64_t)p->Mb * p->bm;
   const size_t line = mlp2::kLine * 4;
   size_t off = 0, z_off[mlp2::kChainMaxLayers] = {}, r_off[mlp2::kChainMaxLayers] = {};
   for (int l = 0; l + 1 < layers; ++l) {
@@ -1371,7 +1381,7 @@ int launch_chain_plan(const mlp2_chain_s* p, const void* X, const void* const* W
   a.trace = p->trace;
   a.trace_cap = p->trace_cap;
   a.trace_groups = p->grid;
-  const int64_t Mpad = (int64_t)p->Mb * p->bt;
+  const int64_t Mpad = (int64_t)p->Mb * p->bm;
   for (int l = 0; l < p->L; ++l) {
     mlp2::ChainLayer& L = c.layer[l];
     L.A = l == 0 ? (const uint16_t*)X : p->Z[l - 1];

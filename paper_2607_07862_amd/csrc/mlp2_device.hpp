@@ -56,11 +56,12 @@ enum {
   CTRL_TICKET = 3 * kLine,         // CTRL_TICKET + l * kLine: next ticket of claim list l (up to 16 lists:
                                    // 8 per role when the pipelined launch splits the grid into roles)
   CTRL_DONE = 19 * kLine,          // CTRL_DONE + l * kLine: finished work-groups of claim list l
-  CTRL_QHEAD = 35 * kLine,         // workqueue mode: next queue slot a consumer claims
-  CTRL_QTAIL = 36 * kLine,         // workqueue mode: next queue slot a producer fills
-  CTRL_EPOCH_WQ = 37 * kLine,      // workqueue runs completed (the scoreboards advance in those only)
-  CTRL_EPOCH_SN = 38 * kLine,      // sentinel runs completed (their parity picks the intermediate buffer)
-  CTRL_WORDS = 39 * kLine
+  CTRL_QHEAD = 35 * kLine,         // workqueue mode: CTRL_QHEAD + l * kLine: queue slots that consumers of
+                                   // claim list l have claimed (8 lists)
+  CTRL_QTAIL = 43 * kLine,         // workqueue mode: next queue slot a producer fills
+  CTRL_EPOCH_WQ = 44 * kLine,      // workqueue runs completed (the scoreboards advance in those only)
+  CTRL_EPOCH_SN = 45 * kLine,      // sentinel runs completed (their parity picks the intermediate buffer)
+  CTRL_WORDS = 46 * kLine
 };
 __device__ __forceinline__ int ctrl_ticket(int l) { return CTRL_TICKET + l * kLine; }
 __device__ __forceinline__ int ctrl_done(int l) { return CTRL_DONE + l * kLine; }
@@ -239,11 +240,15 @@ struct Tile {
   // the ping-pong mainloop (below), whose waves own 64 x 32 blocks of the four
   // 128 x 128 quadrants instead of one contiguous block.
   static constexpr bool QUAD = BM == 256 && WM == 2 && WN == 4 && NS == 2 && BK_ == 64 && (BN == 128 || BN == 256);
+  // The pair tile: 256 x 128 with a three-stage ring, the same loop over two
+  // 128 x 128 halves (for products with too few 256 x 256 tiles).
+  static constexpr bool PAIR = BM == 256 && WM == 2 && WN == 4 && NS == 3 && BK_ == 64 && BN == 128;
+  static constexpr bool HALVES = QUAD || PAIR;  // waves own 64-row blocks of both row halves
   // First row of row block tm, and first column of block pair tp, of the wave at (wm, wn).
   __device__ static constexpr int row_of(int wm, int tm) {
-    return QUAD ? 64 * wm + 16 * (tm & 3) + 128 * (tm >> 2) : wm * MW + 16 * tm;
+    return HALVES ? 64 * wm + 16 * (tm & 3) + 128 * (tm >> 2) : wm * MW + 16 * tm;
   }
-  __device__ static constexpr int col_of(int wn, int tp) { return QUAD ? 32 * wn + 128 * tp : wn * NW + 32 * tp; }
+  __device__ static constexpr int col_of(int wn, int tp) { return HALVES ? 32 * wn + 128 * tp : wn * NW + 32 * tp; }
   static_assert(TM >= 1 && TN >= 2 && TN % 2 == 0, "wave tile shape");
   static constexpr int A_BYTES = BM * BK * 2;
   static constexpr int B_BYTES = BK * BN * 2;
@@ -651,6 +656,201 @@ __device__ __forceinline__ void mainloop_quad(const uint16_t* __restrict__ A, lo
   __syncthreads();  // every wave is done reading the ring before it is reused
 }
 
+// The mainloop of the pair tile (Tile::PAIR): 256 rows by 128 columns, as the
+// quadrant tile's with one column half and so two phases a stage:
+//   memory slot 0 of stage it: read B of stage it;             request B of it + 2
+//               1:             read A1 of it and A0 of it + 1; request A1 of it + 2, A0 of it + 3
+// Three stages of 48 KB (144 KB): every half tile is requested four phases
+// before it is read, and two phases after its ring slot was; the waits and
+// barriers are placed as in the quadrant tile's loop, whose visibility and
+// reuse arguments hold unchanged.
+template <class T, class Wait>
+__device__ __forceinline__ void mainloop_pair(const uint16_t* __restrict__ A, long lda, int m0, int mlast,
+                                              const uint16_t* B, int n0, long ldb, int kbeg, int kend,
+                                              f32x4 (&acc)[T::TN][T::TM], char* lds, Wait& wait, TraceAcc& tr) {
+  static_assert(T::PAIR && T::TM == 8 && T::TN == 2 && T::NWAVES == 8, "pair tile");
+  int tid = threadIdx.x;
+  asm volatile("" : "+v"(tid));  // per-lane offsets are derived per call, as in the plain mainloop
+  const int lane = tid & 63;
+  const int wave = uniform(tid >> 6);
+  const int wm = wave % T::WM, wn = wave / T::WM;
+  const bool trailing = wave >= 4;
+
+#pragma unroll
+  for (int i = 0; i < T::TN; ++i)
+#pragma unroll
+    for (int j = 0; j < T::TM; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  const int nk = (kend - kbeg) / 64;
+  if (nk <= 0) return;
+
+  constexpr uint32_t kHalf = 16384, kA1 = 3 * kHalf, kB = 6 * kHalf;  // LDS: A0, A1 and B, three stages each
+  const uint32_t lds_base = (uint32_t)(uintptr_t)lds;
+  uint32_t a_off[4], b_off[2];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const int row = 8 * (wave + 8 * j) + lane / 8;
+    int gr = m0 + row;
+    gr = gr > mlast ? mlast : gr;
+    a_off[j] = (uint32_t)(((long)gr * lda + 8 * ((lane & 7) ^ swz_a<64>(row))) * 2);
+  }
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    const int row = 4 * (wave + 8 * j) + lane / 16;
+    const int col = n0 + 8 * ((lane & 15) ^ swz_b<128>(row));
+    b_off[j] = (uint32_t)(((long)row * ldb + min(col, (int)ldb - 8)) * 2);
+  }
+  const uint16_t* pa = A + kbeg;
+  const uint16_t* pb = B + (long)kbeg * ldb;
+  auto load_a = [&](int half, int st, int slot) {
+    const uint32_t dst = lds_base + (half ? kA1 : 0u) + (uint32_t)slot * kHalf + (uint32_t)wave * 1024u;
+#pragma unroll
+    for (int j = 0; j < 2; ++j) dma16(pa + (long)st * 64, a_off[2 * half + j], uniform(dst + 8192u * j));
+  };
+  auto load_b = [&](int st, int slot) {
+    const uint32_t dst = lds_base + kB + (uint32_t)slot * kHalf + (uint32_t)wave * 1024u;
+#pragma unroll
+    for (int j = 0; j < 2; ++j) dma16(pb + (long)st * 64 * ldb, b_off[j], uniform(dst + 8192u * j));
+  };
+
+  // Fragment addresses inside a half tile.
+  const int arow = T::row_of(wm, 0) + (lane & 15);
+  uint32_t a_frag[2];
+#pragma unroll
+  for (int ks = 0; ks < 2; ++ks) a_frag[ks] = (uint32_t)(arow * 128 + (((4 * ks + (lane >> 4)) ^ swz_a<64>(arow)) << 4));
+  const int brow = 8 * (lane >> 4) + ((lane & 15) >> 2);
+  const uint32_t b_frag = kB + (uint32_t)(brow * 256 + (((4 * wn + (lane & 3)) ^ swz_b<128>(brow)) << 4));
+
+  bf16x8 x0[2][4], x1[2][4], w[2][2];
+  auto read_a = [&](bf16x8 (&x)[2][4], int half, int slot) {
+    const char* base = lds + (half ? kA1 : 0u) + slot * kHalf;
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+      for (int tm = 0; tm < 4; ++tm) x[ks][tm] = *reinterpret_cast<const bf16x8*>(base + a_frag[ks] + tm * 2048);
+  };
+  auto read_b = [&](int slot) {
+    const char* base = lds + slot * kHalf;
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        const char* p = base + b_frag + ks * 8192 + i * 8;
+        bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4_t*)(p));
+        bf16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4_t*)(p + 1024));
+        w[ks][i] = (bf16x8)__builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+      }
+  };
+  auto mma = [&](const bf16x8 (&x)[2][4], auto half) {
+    constexpr int a = decltype(half)::value * 4;
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int tm = 0; tm < 4; ++tm)
+          acc[i][a + tm] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[ks][i], x[ks][tm], acc[i][a + tm], 0, 0, 0);
+  };
+  auto slot_end = [&]() {
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  auto vm_traced = [&](auto n) {
+    const uint64_t t0 = trace_now();
+    wait_vm<decltype(n)::value>();
+    if constexpr (kTrace) tr.ring += trace_now() - t0;
+  };
+  auto products = [&](const bf16x8 (&x)[2][4], auto half) {
+    __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): this wave's fragment reads are complete
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_setprio(1);
+    mma(x, half);
+    __builtin_amdgcn_s_setprio(0);
+    slot_end();
+  };
+
+  // One stage.  LEFT: stages after it, counted up to 3; r: its ring slot.
+  int r = 0;
+  auto stage = [&](int it, auto left_) {
+    constexpr int LEFT = decltype(left_)::value;
+    const int r1 = r == 2 ? 0 : r + 1, r2 = r == 0 ? 2 : r - 1;  // (r + 1, r + 2) % 3
+    if constexpr (LEFT >= 2) load_b(it + 2, r2);
+    read_b(r);
+    if constexpr (LEFT >= 3) {
+      const int k = kbeg + (it + 3) * 64;
+      if (Wait::kBlocks && wave == 0) wait.leader(k);
+      wait.known(k);
+    }
+    vm_traced(int_constant<LEFT >= 2 ? 8 : LEFT == 1 ? 4 : 0>());  // A1 of this stage, A0 of the next
+    slot_end();
+    products(x0, int_constant<0>());
+
+    if constexpr (LEFT >= 2) load_a(1, it + 2, r2);
+    if constexpr (LEFT >= 3) load_a(0, it + 3, r);
+    read_a(x1, 1, r);
+    if constexpr (LEFT >= 1) {
+      read_a(x0, 0, r1);
+      vm_traced(int_constant<LEFT >= 3 ? 10 : LEFT == 2 ? 8 : 2>());  // B of the next stage
+    }
+    slot_end();
+    products(x1, int_constant<1>());
+    r = r1;
+  };
+
+  // Prologue: the first two stages, and A0 of the third.
+  if constexpr (Wait::kBlocks) {  // the weights stream while the item waits for its rows
+    load_b(0, 0);
+    if (nk > 1) load_b(1, 1);
+    if (wave == 0) {
+      wait.leader(kbeg);
+      if (nk > 1) wait.leader(kbeg + 64);
+      if (nk > 2) wait.leader(kbeg + 128);
+    }
+    slot_end();
+    load_a(0, 0, 0);
+    load_a(1, 0, 0);
+    if (nk > 1) {
+      load_a(0, 1, 1);
+      load_a(1, 1, 1);
+    }
+    if (nk > 2) load_a(0, 2, 2);
+    wait_vm<0>();  // requested out of the stage order, so nothing less covers it
+  } else {
+    load_a(0, 0, 0);
+    load_b(0, 0);
+    load_a(1, 0, 0);
+    if (nk > 1) {
+      load_a(0, 1, 1);
+      load_b(1, 1);
+      load_a(1, 1, 1);
+    }
+    if (nk > 2) {
+      load_a(0, 2, 2);
+      wait_vm<10>();  // A0, B
+    } else if (nk == 2) {
+      wait_vm<8>();
+    } else {
+      wait_vm<2>();
+    }
+  }
+  wait.known(kbeg);
+  if (nk > 1) wait.known(kbeg + 64);
+  if (nk > 2) wait.known(kbeg + 128);
+  slot_end();
+  read_a(x0, 0, 0);
+  __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
+
+  if (trailing) slot_end();
+  for (int it = 0; it < nk - 3; ++it) stage(it, int_constant<3>());
+  if (nk > 2) stage(nk - 3, int_constant<2>());
+  if (nk > 1) stage(nk - 2, int_constant<1>());
+  stage(nk - 1, int_constant<0>());
+  if (!trailing) slot_end();
+  __syncthreads();  // every wave is done reading the ring before it is reused
+}
+
 template <class T, int NB, class Wait, class Check = NoCheck>
 __device__ __forceinline__ void mainloop(const uint16_t* __restrict__ A, long lda, int m0, int mlast,
                                          const uint16_t* const (&Bp)[NB], const int (&n0)[NB], long ldb, int kbeg,
@@ -658,6 +858,10 @@ __device__ __forceinline__ void mainloop(const uint16_t* __restrict__ A, long ld
                                          Check check = Check()) {
   if constexpr (T::QUAD && NB * T::BN == 256 && is_same_type<Check, NoCheck>::value) {
     mainloop_quad<T, NB>(A, lda, m0, mlast, Bp, n0, ldb, kbeg, kend, acc, lds, wait, tr);
+    return;
+  }
+  if constexpr (T::PAIR && NB == 1 && is_same_type<Check, NoCheck>::value) {
+    mainloop_pair<T>(A, lda, m0, mlast, Bp[0], n0[0], ldb, kbeg, kend, acc[0], lds, wait, tr);
     return;
   }
   // The thread index passes through an empty asm, so the compiler derives
@@ -1408,7 +1612,9 @@ __device__ __forceinline__ void push_ready(const Args& a, int tile, uint32_t wq_
   }
 }
 
-// Consumer side: wave 0 claims the next queue slot and polls it (every lane
+// Consumer side: wave 0 claims the next queue slot of the work-group's claim
+// list (list l of L has slots l, l + L, ...: hundreds of work-groups claiming
+// at once from one word took turns for microseconds) and polls it (every lane
 // at the same address, a scalar loop with uniform exits) until a producer of
 // this run has filled it, sleeping between polls; after spin_limit polls, or
 // once another wait gave up, it latches CTRL_ERROR and returns no unit.
@@ -1422,8 +1628,10 @@ __device__ __forceinline__ int pop_ready(const Args& a, uint32_t wq_epoch, int* 
   if (uniform((int)(threadIdx.x >> 6)) == 0) {  // wave 0, as a scalar branch
     const int lane = threadIdx.x & 63;
     uint32_t h = 0;
-    if (lane == 0) h = __hip_atomic_fetch_add(a.ctrl + CTRL_QHEAD, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    h = uniform(h);
+    const uint32_t lists = (uint32_t)a.lists, l = (uint32_t)blockIdx.x % lists;
+    if (lane == 0)
+      h = __hip_atomic_fetch_add(a.ctrl + CTRL_QHEAD + l * kLine, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    h = l + lists * uniform(h);
     int q = -1;
     if (h < (uint32_t)a.items2) {
       const uint32_t want = uniform(queue_tag(wq_epoch));

@@ -412,7 +412,8 @@ __device__ __forceinline__ void finish_kernel(const Args& a, bool roles, uint32_
       const uint32_t all_lists = (uint32_t)(lp.role < 0 ? a.lists : a.lists + a.lists2);
       if (lists_done == all_lists - 1u) {
         __hip_atomic_store(a.ctrl + CTRL_DONE_ALL, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __hip_atomic_store(a.ctrl + CTRL_QHEAD, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        for (int l = 0; l < 8; ++l)
+          __hip_atomic_store(a.ctrl + CTRL_QHEAD + l * kLine, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         __hip_atomic_store(a.ctrl + CTRL_QTAIL, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (wq_run) __hip_atomic_store(a.ctrl + CTRL_EPOCH_WQ, wq_epoch + 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (sn_run) __hip_atomic_store(a.ctrl + CTRL_EPOCH_SN, sn_epoch + 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -626,6 +627,7 @@ template <int NS> struct TileFor<128, 64, NS, 8> { using type = Tile<128, 64, 4,
 template <int NS> struct TileFor<64, 256, NS, 8> { using type = Tile<64, 256, 2, 4, NS>; };
 template <int NS> struct TileFor<32, 256, NS, 8> { using type = Tile<32, 256, 1, 8, NS>; };
 template <> struct TileFor<256, 128, 2, 8> { using type = Tile<256, 128, 2, 4, 2>; };  // the quadrant tile
+template <> struct TileFor<256, 128, 3, 8> { using type = Tile<256, 128, 2, 4, 3>; };  // the pair tile
 template <int BM, int BN, int NS, int W, int BK, bool WNT = false>
 struct TileForK {
   using base = typename TileFor<BM, BN, NS, W>::type;
@@ -704,7 +706,7 @@ static const Entry* find_entry(const KernelConfig& c) {
 // An L-layer chain Z_l = act(Z_{l-1} W_l), Y = Z_{L-1} W_L: the producer /
 // consumer relation of the two-layer kernel at every layer boundary (Sec.
 // III-A).  An item is a T output tile of one layer over its whole K: 256 x
-// 256 over eight waves with a two-stage ring for chains of many rows, 128 x
+// 256 or 256 x 128 over eight waves for chains of many rows, 128 x
 // 128 over four waves (two work-groups per CU), or 64 x 64 with four stages
 // for chains of few rows, whose larger tiles would leave most CUs idle.
 // A middle layer's item consumes like a GEMM2 item (it waits per K-slice on
@@ -719,7 +721,8 @@ static const Entry* find_entry(const KernelConfig& c) {
 using ChainT128 = TileFor<128, 128, 2>::type;
 using ChainT64 = TileFor<64, 64, 4>::type;
 using ChainT256 = TileFor<256, 256, 2, 8>::type;
-static_assert(ChainT128::NWAVES == 4 && ChainT64::NWAVES == 4 && ChainT256::NWAVES == 8, "chain tile waves");
+using ChainPair = TileFor<256, 128, 3, 8>::type;
+static_assert(ChainT128::NWAVES == 4 && ChainT64::NWAVES == 4 && ChainT256::NWAVES == 8 && ChainPair::PAIR, "chain tile waves");
 
 template <class T>
 __device__ __forceinline__ void chain_item(const ChainArgs& c, int layer, int tile, uint32_t epoch, char* lds,
@@ -803,18 +806,19 @@ __global__ __launch_bounds__(T::THREADS, T::NWAVES == 4 ? 2 : 1) void k_mlp2_cha
 static const void* chain_kernel(int tile) {
   return tile == 0   ? (const void*)&k_mlp2_chain<ChainT128>
          : tile == 1 ? (const void*)&k_mlp2_chain<ChainT64>
-                     : (const void*)&k_mlp2_chain<ChainT256>;
+         : tile == 2 ? (const void*)&k_mlp2_chain<ChainT256>
+                     : (const void*)&k_mlp2_chain<ChainPair>;
 }
 
-static int chain_threads(int tile) { return tile == 2 ? ChainT256::THREADS : ChainT128::THREADS; }
+static int chain_threads(int tile) { return tile >= 2 ? ChainT256::THREADS : ChainT128::THREADS; }
 
 hipError_t chain_occupancy(int tile, int* blocks_per_cu) {
-  if (tile < 0 || tile > 2) return hipErrorInvalidValue;
+  if (tile < 0 || tile > 3) return hipErrorInvalidValue;
   return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, chain_kernel(tile), chain_threads(tile), 0);
 }
 
 hipError_t launch_chain(int tile, const ChainArgs& c, int grid, hipStream_t stream) {
-  if (tile < 0 || tile > 2) return hipErrorInvalidValue;
+  if (tile < 0 || tile > 3) return hipErrorInvalidValue;
   void* args[] = {const_cast<ChainArgs*>(&c)};
   return hipLaunchKernel(chain_kernel(tile), dim3(grid), dim3(chain_threads(tile)), args, 0, stream);
 }

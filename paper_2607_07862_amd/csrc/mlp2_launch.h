@@ -31,8 +31,9 @@ hipError_t launch_sentinel(const KernelConfig& c, const Args& a, int grid, hipSt
 constexpr int kChainMaxLayers = 8;
 constexpr int kChainWidthUnit = 128;  // every width is a multiple of this
 // Tile shapes of the chain kernel: 0 = 128 x 128 (four waves, two-stage ring), 1 = 64 x 64 (four
-// waves, four stages), 2 = 256 x 256 (eight waves, two-stage ring).
-constexpr int kChainTiles[3] = {128, 64, 256};
+// waves, four stages), 2 = 256 x 256 and 3 = 256 x 128 (eight waves, ping-pong loops).
+constexpr int kChainRows[4] = {128, 64, 256, 256};
+constexpr int kChainCols[4] = {128, 64, 256, 128};
 
 // One layer of a chain launch (passed by value with every launch).
 struct ChainLayer {
