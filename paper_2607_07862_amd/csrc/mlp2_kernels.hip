@@ -486,8 +486,8 @@ constexpr int min_blocks() {
 
 // Reads one word of each 64-byte line of the kernel's arguments, all at once:
 // the scalar loads the compiler places where a field is first used then hit the
-// scalar cache instead of each waiting for its own line.  (64 x 512 x 2048:
-// with the epochs waited for late, below, 12.3 -> 11.8 us; either alone 12.3.)
+// scalar cache instead of each waiting for its own line (64 x 512 x 2048: 12.3
+// -> 11.9 us).
 template <int BYTES>
 __device__ __forceinline__ void touch_args() {
   const int* k = (const int*)__builtin_amdgcn_kernarg_segment_ptr();
@@ -506,6 +506,18 @@ __global__ __launch_bounds__(T1::THREADS, (min_blocks<T1, NB, T2, HV, PHASE>()))
   __shared__ __attribute__((aligned(1024))) char lds[kLds];
   __shared__ int s_item, s_slot;
   touch_args<(int)sizeof(Args)>();
+  const uint32_t epoch = uniform(ld_relaxed(a.ctrl + CTRL_EPOCH));
+  const uint32_t wq_epoch = PHASE == PHASE_WORKQUEUE ? uniform(ld_relaxed(a.ctrl + CTRL_EPOCH_WQ)) : 0u;
+  // Sentinel runs alternate between two intermediates: this run's producers
+  // write one and refill the other with sentinels for the next sentinel run.
+  const uint32_t sn_epoch =
+      PHASE == PHASE_SENTINEL || PHASE == PHASE_PIPELINED ? uniform(ld_relaxed(a.ctrl + CTRL_EPOCH_SN)) : 0u;
+  // Earlier runs whose GEMM1 tiles signalled the ready counters: every run but the sentinel runs.
+  const uint32_t ready_runs = epoch - sn_epoch;
+  if constexpr (PHASE == PHASE_SENTINEL) {
+    a.Z = a.Zs + (long)(sn_epoch & 1u) * a.zs_elems;
+    a.Zr = a.Zs + (long)((sn_epoch + 1u) & 1u) * a.zs_elems;
+  }
   // A role split (pipelined launch only): this work-group takes the items of
   // one kind, in that kind's order table; otherwise both kinds from one order.
   const ListPos lp = list_pos(a, PHASE == PHASE_PIPELINED && a.p1 > 0);
@@ -514,50 +526,15 @@ __global__ __launch_bounds__(T1::THREADS, (min_blocks<T1, NB, T2, HV, PHASE>()))
   // reduction items (ranked last) in the launches that sum split-K tiles with them
   const int gr = (PHASE == PHASE_GEMM2 || PHASE == PHASE_PIPELINED) && lp.role != 0 ? a.items_red : 0;
   const int total = g1 + g2 + gr;
-  // The order-table entry of rank p: item id, and (pipelined and sentinel
-  // launches) bit 31 set for a GEMM2 item, with bit 30 for a reduction item.
-  auto entry = [&](int p) -> uint32_t {
-    if constexpr (PHASE == PHASE_SENTINEL) return a.orderp[p];
-    else if constexpr (PHASE == PHASE_PIPELINED) return lp.role < 0 ? a.orderp[p] : lp.role == 0 ? a.order1[p] : (a.order2[p] | 0x80000000u);
-    else if constexpr (PHASE == PHASE_GEMM2) return a.order2[p];
-    else return a.order1[p];
-  };
-  // The first item's table entry is requested before the epochs, and the
-  // epochs are waited for at their first use, which is the end of an item that
-  // never waits.  (The opaque index keeps them in vector registers; the
-  // compiler would otherwise wait for them here to make scalars of them.)
-  int lane0 = 0;
-  asm volatile("" : "+v"(lane0));
-  const uint32_t* ctrl = a.ctrl + lane0;
-  const bool fixed = lp.role < 0 && (int)blockIdx.x < a.first_static;
-  uint32_t e = fixed ? entry((int)blockIdx.x) : 0u;
-  uint32_t epoch = ld_relaxed(ctrl + CTRL_EPOCH);
-  uint32_t wq_epoch = PHASE == PHASE_WORKQUEUE ? ld_relaxed(ctrl + CTRL_EPOCH_WQ) : 0u;
-  // Sentinel runs alternate between two intermediates: this run's producers
-  // write one and refill the other with sentinels for the next sentinel run.
-  uint32_t sn_epoch = PHASE == PHASE_SENTINEL || PHASE == PHASE_PIPELINED ? ld_relaxed(ctrl + CTRL_EPOCH_SN) : 0u;
   int p;
-  if (fixed) {
+  if (lp.role < 0 && (int)blockIdx.x < a.first_static) {
     p = (int)blockIdx.x;
-    e = uniform(e);
   } else {
     Claim first = make_claim(a, lp.role >= 0);
     first.issue();
     first.park(&s_item);
     __syncthreads();
     p = uniform(s_item);
-    e = p < total ? uniform(entry(p)) : 0u;
-  }
-  if constexpr (T1::QUAD || T2::QUAD || PHASE == PHASE_SENTINEL || PHASE == PHASE_WORKQUEUE) {
-    epoch = uniform(epoch);  // no vector register to spare through the mainloop
-    sn_epoch = uniform(sn_epoch);
-    wq_epoch = uniform(wq_epoch);
-  }
-  // Earlier runs whose GEMM1 tiles signalled the ready counters: every run but the sentinel runs.
-  const uint32_t ready_runs = epoch - sn_epoch;
-  if constexpr (PHASE == PHASE_SENTINEL) {
-    a.Z = a.Zs + (long)(sn_epoch & 1u) * a.zs_elems;
-    a.Zr = a.Zs + (long)((sn_epoch + 1u) & 1u) * a.zs_elems;
   }
   int n_items = 0;
   for (;;) {
@@ -567,12 +544,15 @@ __global__ __launch_bounds__(T1::THREADS, (min_blocks<T1, NB, T2, HV, PHASE>()))
     if constexpr (kTrace) tr.c_start = trace_clock();
     const uint64_t t_start = trace_now();
     Claim next = make_claim(a, lp.role >= 0);
+    uint32_t e;  // order-table entry: item id, bit 31 set for a GEMM2 item
     if constexpr (PHASE == PHASE_SENTINEL) {
+      e = uniform(a.orderp[p]);
       if (e & 0x80000000u)
         gemm2_item<T2, HV, false, Claim, true>(a, (int)(e & 0x7fffffffu), epoch, lds, &s_slot, next, &s_item, tr);
       else
         gemm1_item<T1, NB, false, true>(a, (int)e, epoch, lds, &s_slot, next, &s_item, tr);
     } else if constexpr (PHASE == PHASE_PIPELINED) {
+      e = lp.role < 0 ? uniform(a.orderp[p]) : lp.role == 0 ? uniform(a.order1[p]) : (uniform(a.order2[p]) | 0x80000000u);
       if ((e & 0xc0000000u) == 0xc0000000u)
         reduce_item<T2, HV>(a, (int)(e & 0x3fffffffu), epoch, &s_slot, next, &s_item, tr);
       else if (e & 0x80000000u)
@@ -580,8 +560,10 @@ __global__ __launch_bounds__(T1::THREADS, (min_blocks<T1, NB, T2, HV, PHASE>()))
       else
         gemm1_item<T1, NB>(a, (int)e, epoch, lds, &s_slot, next, &s_item, tr);
     } else if constexpr (PHASE == PHASE_GEMM1 || PHASE == PHASE_WORKQUEUE) {
+      e = uniform(a.order1[p]);
       gemm1_item<T1, NB, PHASE == PHASE_WORKQUEUE, false, PHASE != PHASE_GEMM1>(a, (int)e, epoch, lds, &s_slot, next, &s_item, tr, wq_epoch);
     } else {
+      e = uniform(a.order2[p]);
       if (e & 0x40000000u)
         reduce_item<T2, HV>(a, (int)(e & 0x3fffffffu), epoch, &s_slot, next, &s_item, tr);
       else
@@ -591,7 +573,6 @@ __global__ __launch_bounds__(T1::THREADS, (min_blocks<T1, NB, T2, HV, PHASE>()))
     if constexpr (kTrace) tr_record(a, PHASE == PHASE_GEMM2 ? 1 : 0, n_items++, p, e, t_start, tr);
     __syncthreads();
     p = uniform(s_item);
-    if (p < total) e = uniform(entry(p));
   }
   if constexpr (PHASE == PHASE_WORKQUEUE) {
     __syncthreads();  // every wave is done with s_item before pop_ready rewrites it
