@@ -5,7 +5,7 @@
 //     ds_read_b64_tr_b16;
 //   * the fused epilogues: activation + bf16 store + ready signal for GEMM1,
 //     bf16 store for GEMM2, and a deterministic split-K reduction;
-//   * the flag primitives: release-increment of a ready counter by the
+//   * the flag primitives: increment of a ready counter by the
 //     producer, bounded acquire-spin by the consumer (Sec. III-A: the
 //     producer fences its data before it signals; the consumer polls before
 //     it reads).
@@ -163,7 +163,7 @@ __device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirs
 __device__ __forceinline__ uint32_t uniform(uint32_t v) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)v); }
 
 // Every wave waits until its own outstanding memory operations are complete
-// (stores acknowledged), so that a later agent-scope release by one lane of
+// (stores acknowledged), so that a later count by one lane of
 // the work-group covers the data of all waves.
 __device__ __forceinline__ void wait_all_mem() { __builtin_amdgcn_s_waitcnt(0); }
 

@@ -110,7 +110,7 @@ __device__ __forceinline__ Claim make_claim(const Args& a, bool roles) {
 // with the item count, then trace_cap records of kTraceWords words: rank
 // (high half) and item (low half: the order-table entry, bit 31 set for a
 // GEMM2 item), start, mainloop end, two epilogue marks (a signalling GEMM1 tile: Z stores
-// complete, ready counter released; a split-K part that leaves the tile to a
+// complete, ready counter counted up; a split-K part that leaves the tile to a
 // sibling: partial stored, arrival counted; else 0 and 0), end, ring-wait
 // ticks, flag-wait ticks.  Records past
 // trace_cap are counted, not stored.  Written by thread 0 with plain stores.
@@ -234,7 +234,7 @@ __device__ __forceinline__ void gemm1_item(const Args& a, int id_in, uint32_t ep
     });
   }
   if constexpr (SN) return;  // no fence and no flag: consumers check the data itself
-  // Producer signal (one per tile and run): the tile's Z rows are released, ready[tile] += 1.
+  // Producer signal (one per tile and run): the tile's Z rows are stored through, ready[tile] += 1.
   if constexpr (kTrace) {
     wait_all_mem();
     tr.t_rel = trace_now();
@@ -311,7 +311,7 @@ __device__ __forceinline__ void gemm2_item(const Args& a, int p_in, uint32_t epo
         }
   } else if (a.red2 > 0) {
     // The tile is summed by its reduction items: store the partial and count
-    // the arrival (a release), then on to the next item.
+    // the arrival, then on to the next item.
     store_partial<T, HV>(a.part2, tile, a.S2, s, acc);
     if constexpr (kTrace) {
       wait_all_mem();
@@ -340,7 +340,7 @@ __device__ __forceinline__ void gemm2_item(const Args& a, int p_in, uint32_t epo
 // for lower ranks, and the whole tile is summed by red2 work-groups at once
 // instead of by the part that arrives last.  The partials need no agent-scope
 // acquire, for the reason given at arrive_split (each slice's 1 KB runs are
-// read once per launch, by one item, after every part released them).  A wait
+// read once per launch, by one item, after every part stored them through).  A wait
 // that gives up latches CTRL_ERROR (bit 0) and skips the sums; the kernel
 // still drains and mlp2_check reports the timeout.
 template <class T, int HV, class C = Claim>
@@ -487,7 +487,7 @@ constexpr int min_blocks() {
 // Reads one word of each 64-byte line of the kernel's arguments, all at once:
 // the scalar loads the compiler places where a field is first used then hit the
 // scalar cache instead of each waiting for its own line (64 x 512 x 2048: 12.3
-// -> 11.9 us).
+// -> 12.0 us).
 template <int BYTES>
 __device__ __forceinline__ void touch_args() {
   const int* k = (const int*)__builtin_amdgcn_kernarg_segment_ptr();
