@@ -1186,14 +1186,17 @@ struct SentinelCheck {
 // Output coordinates held by this lane for block pair tp and row block tm.
 template <class T>
 struct FragPos {
-  int row0, col0;
+  int row0, col0, block0;
   __device__ FragPos(int m0, int n0) {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, wave = uniform((int)(threadIdx.x >> 6));
     row0 = m0 + T::row_of(wave % T::WM, 0) + (lane & 15);
-    col0 = n0 + T::col_of(wave / T::WM, 0) + 8 * (lane >> 4);
+    block0 = n0 + T::col_of(wave / T::WM, 0);
+    col0 = block0 + 8 * (lane >> 4);
   }
   __device__ int row(int tm) const { return row0 + T::row_of(0, tm); }
   __device__ int col(int tp) const { return col0 + T::col_of(0, tp); }
+  // first of the wave's 32 columns of block pair tp, a scalar
+  __device__ int block(int tp) const { return block0 + T::col_of(0, tp); }
 };
 
 template <class T>
@@ -1256,7 +1259,8 @@ struct Unit {
   }
   // Output row and first of the 8 consecutive columns held by `lane` of this unit.
   __device__ int row(int m0, int lane) const { return m0 + T::row_of(w % T::WM, tm) + (lane & 15); }
-  __device__ int col(int n0, int lane) const { return n0 + T::col_of(w / T::WM, tp) + 8 * (lane >> 4); }
+  __device__ int block(int n0) const { return n0 + T::col_of(w / T::WM, tp); }  // the unit's first column
+  __device__ int col(int n0, int lane) const { return block(n0) + 8 * (lane >> 4); }
 };
 
 // v[g][b][0..7] = sum over s = 0 .. S-1 (in that order) of the 8 values of

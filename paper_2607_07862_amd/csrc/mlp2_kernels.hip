@@ -27,6 +27,11 @@ namespace mlp2 {
 
 // GEMM1 epilogue for one lane: activation in fp32 on the 8 consecutive values
 // of row `row` from column `col`, round to bf16, one 16-byte store into Z.
+// The last column block may be wider than what is left: the callers of
+// store_z and store_y skip the blocks of 32 columns past the width, by the
+// block's first column, a scalar (the widths are multiples of 64).  A test of
+// each lane's own column would put the stores under a lane mask, and with them
+// the barrier of the signal that follows.
 // PUB: published inside the launch (stored through); the GEMM1 kernel's Z is
 // read by the next kernel only.
 template <int NB, bool SN = false, bool PUB = true>
@@ -44,7 +49,6 @@ __device__ __forceinline__ void store_z(const Args& a, long row, int col, const 
     }
   }
   const u32x4 packed = canonicalize_z(pack_bf16x8(z));  // never the sentinel pattern
-  if (col >= a.F) return;                               // the last column block may be wider than what is left
   if constexpr (SN) {
     // Sentinel mode: the piece goes straight to the device's point of
     // coherence, with no fence or flag after it; the same piece of the next
@@ -60,7 +64,7 @@ __device__ __forceinline__ void store_z(const Args& a, long row, int col, const 
 }
 
 __device__ __forceinline__ void store_y(const Args& a, int row, int col, const float (&v)[8]) {
-  if (row < a.M && col < a.H) *reinterpret_cast<u32x4*>(a.Y + (long)row * a.H + col) = pack_bf16x8(v);
+  if (row < a.M) *reinterpret_cast<u32x4*>(a.Y + (long)row * a.H + col) = pack_bf16x8(v);
 }
 
 // Claim lists.  Work-groups are placed on the XCDs round-robin by index, so
@@ -222,7 +226,7 @@ __device__ __forceinline__ void gemm1_item(const Args& a, int id_in, uint32_t ep
         float v[NB][8];
 #pragma unroll
         for (int b = 0; b < NB; ++b) pair_values<T>(acc[b], tp, tm, v[b]);
-        store_z<NB, SN, PUB>(a, fp.row(tm), fp.col(tp), v, tile != a.drop_signal);
+        if (fp.block(tp) < a.F) store_z<NB, SN, PUB>(a, fp.row(tm), fp.col(tp), v, tile != a.drop_signal);
       }
   } else {
     const bool last = arrive_split<T, NB>(a.part1, a.cnt1 + (long)tile * kLine, tile, a.S1, s,
@@ -230,7 +234,7 @@ __device__ __forceinline__ void gemm1_item(const Args& a, int id_in, uint32_t ep
     next.park(s_next);
     if (!last) return;
     reduce_epilogue<T, NB>(a.part1, tile, a.S1, [&](const Unit<T>& u, int lane, const float (&v)[NB][8]) {
-      store_z<NB, SN, PUB>(a, u.row(m0, lane), u.col(n0, lane), v, tile != a.drop_signal);
+      if (u.block(n0) < a.F) store_z<NB, SN, PUB>(a, u.row(m0, lane), u.col(n0, lane), v, tile != a.drop_signal);
     });
   }
   if constexpr (SN) return;  // no fence and no flag: consumers check the data itself
@@ -307,7 +311,7 @@ __device__ __forceinline__ void gemm2_item(const Args& a, int p_in, uint32_t epo
         for (int tp = 0; tp < T::TN / 2; ++tp) {
           float v[8];
           pair_values<T>(acc[h], tp, tm, v);
-          store_y(a, fp.row(tm), fp.col(tp) + h * T::BN, v);
+          if (fp.block(tp) + h * T::BN < a.H) store_y(a, fp.row(tm), fp.col(tp) + h * T::BN, v);
         }
   } else if (a.red2 > 0) {
     // The tile is summed by its reduction items: store the partial and count
@@ -327,7 +331,8 @@ __device__ __forceinline__ void gemm2_item(const Args& a, int p_in, uint32_t epo
     if (!last) return;
     reduce_epilogue<T, HV>(a.part2, tile, a.S2, [&](const Unit<T>& u, int lane, const float (&v)[HV][8]) {
 #pragma unroll
-      for (int h = 0; h < HV; ++h) store_y(a, u.row(m0, lane), u.col(n0, lane) + h * T::BN, v[h]);
+      for (int h = 0; h < HV; ++h)
+        if (u.block(n0) + h * T::BN < a.H) store_y(a, u.row(m0, lane), u.col(n0, lane) + h * T::BN, v[h]);
     });
   }
 }
@@ -380,7 +385,8 @@ __device__ __forceinline__ void reduce_item(const Args& a, int r_in, uint32_t ep
   if (ok)
     reduce_slice<T, HV>(a.part2, tile, a.S2, slice, a.red2, [&](const Unit<T>& u, int lane, const float (&v)[HV][8]) {
 #pragma unroll
-      for (int h = 0; h < HV; ++h) store_y(a, u.row(m0, lane), u.col(n0, lane) + h * T::BN, v[h]);
+      for (int h = 0; h < HV; ++h)
+        if (u.block(n0) + h * T::BN < a.H) store_y(a, u.row(m0, lane), u.col(n0, lane) + h * T::BN, v[h]);
     });
   next.park(s_next);
 }
