@@ -160,6 +160,14 @@ __device__ __forceinline__ uint32_t ld_relaxed(const uint32_t* p) {
 // an exec-masked divergent region, in which waves can execute different
 // numbers of s_barrier and deadlock the work-group.
 __device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
+// The thread's index through an empty asm, for what an item derives from it
+// alone: otherwise the compiler computes all of that before the persistent
+// item loop and, in the 256-row kernels, keeps it in scratch memory.
+__device__ __forceinline__ int thread_here() {
+  int t = threadIdx.x;
+  asm volatile("" : "+v"(t));
+  return t;
+}
 __device__ __forceinline__ uint32_t uniform(uint32_t v) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)v); }
 
 // Every wave waits until its own outstanding memory operations are complete
@@ -356,10 +364,10 @@ __device__ __forceinline__ void store_coherent16(uint16_t* p, u32x4 v) {
 // back the XCD's whole L2, once per work-group and item, in turn: at 32 rows
 // and less that was a third to half of the run (figures at release_add).
 // `base` is the same in every lane; `off` is in bytes, below 4 GiB.
-__device__ __forceinline__ void store_through16(void* base, uint32_t off, u32x4 v) {
+__device__ __forceinline__ void store_through16(void* base, uint32_t off, u32x4 v, int step = 0) {
   constexpr int kSc1 = 16;
   const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(base, 0, -1, 0x00027000);
-  __builtin_amdgcn_raw_buffer_store_b128(v, rsrc, (int)off, 0, kSc1);
+  __builtin_amdgcn_raw_buffer_store_b128(v, rsrc, (int)off, step, kSc1);
 }
 
 // Wait until at most n of this wave's vector-memory operations are outstanding.
@@ -1188,7 +1196,7 @@ template <class T>
 struct FragPos {
   int row0, col0, block0;
   __device__ FragPos(int m0, int n0) {
-    const int lane = threadIdx.x & 63, wave = uniform((int)(threadIdx.x >> 6));
+    const int tid = thread_here(), lane = tid & 63, wave = uniform(tid >> 6);
     row0 = m0 + T::row_of(wave % T::WM, 0) + (lane & 15);
     block0 = n0 + T::col_of(wave / T::WM, 0);
     col0 = block0 + 8 * (lane >> 4);
@@ -1235,14 +1243,15 @@ struct Partial {
 template <class T, int NB>
 __device__ __forceinline__ void store_partial(float* base, long tile, int S, int s, const f32x4 (&acc)[NB][T::TN][T::TM]) {
   float* item = base + Partial<T, NB>::block_index(tile, S, s, 0, 0, 0, 0) * 4;
-  const uint32_t off = ((threadIdx.x >> 6) * Partial<T, NB>::PER_WAVE * 64 + (threadIdx.x & 63)) * 16;
+  const uint32_t tid = (uint32_t)thread_here();
+  const uint32_t off = ((tid >> 6) * Partial<T, NB>::PER_WAVE * 64 + (tid & 63)) * 16;
   int i = 0;
 #pragma unroll
   for (int b = 0; b < NB; ++b)
 #pragma unroll
     for (int tn = 0; tn < T::TN; ++tn)
 #pragma unroll
-      for (int tm = 0; tm < T::TM; ++tm, ++i) store_through16(item, off + i * 1024, __builtin_bit_cast(u32x4, acc[b][tn][tm]));
+      for (int tm = 0; tm < T::TM; ++tm, ++i) store_through16(item, off, __builtin_bit_cast(u32x4, acc[b][tn][tm]), i * 1024);
 }
 
 // A reduction unit: wave w's blocks (2 tp, tm) and (2 tp + 1, tm).

@@ -145,9 +145,9 @@ __device__ __forceinline__ void reduce_epilogue(const float* part, long tile, in
   constexpr int U = Partial<T, NB>::UNITS;
   constexpr int G = NB == 1 ? 2 : 1;
   static_assert(U % G == 0, "units per group");
-  const int lane = threadIdx.x & 63;
+  const int tid = thread_here(), lane = tid & 63;
   with_round(S, [&](auto r) {
-    for (int u0 = uniform((int)(threadIdx.x >> 6)) * G; u0 < U; u0 += T::NWAVES * G) {
+    for (int u0 = uniform(tid >> 6) * G; u0 < U; u0 += T::NWAVES * G) {
       Unit<T> ug[G];
 #pragma unroll
       for (int g = 0; g < G; ++g) ug[g] = Unit<T>(u0 + g);
@@ -168,9 +168,9 @@ __device__ __forceinline__ void reduce_slice(const float* part, long tile, int S
   constexpr int G = NB == 1 ? 2 : 1;
   static_assert(U % G == 0, "units per group");
   const int per = U / G / slices;  // groups per slice (the plan makes `slices` divide U / G)
-  const int lane = threadIdx.x & 63;
+  const int tid = thread_here(), lane = tid & 63;
   with_round(S, [&](auto r) {
-    for (int grp = uniform((int)(threadIdx.x >> 6)); grp < per; grp += T::NWAVES) {
+    for (int grp = uniform(tid >> 6); grp < per; grp += T::NWAVES) {
       const int u0 = (slice * per + grp) * G;
       Unit<T> ug[G];
 #pragma unroll

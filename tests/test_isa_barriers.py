@@ -215,3 +215,13 @@ def test_direct_to_lds_loads_read_a_base_moved_by_a_scalar_instruction(asm):
     assert any("global_load_lds" in b for b in ks.values())
     problems = {n: dma_base_hazards(b)[:3] for n, b in ks.items() if dma_base_hazards(b)}
     assert not problems, problems
+
+
+def test_no_kernel_keeps_values_in_scratch_memory(asm):
+    """No spilled vector registers and no private segment: a kernel with one also makes the runtime allocate scratch,
+    in calls whose users may not allocate."""
+    ks = kernels(asm)
+    sizes = dict(re.findall(r"\.name:\s+(_Z\w*k_mlp2\w*)\n(?:.*\n)*?\s*\.private_segment_fixed_size: (\d+)", asm))
+    assert set(sizes) == set(ks)
+    problems = {n: sizes[n] for n, b in ks.items() if int(sizes[n]) or "scratch_" in b}
+    assert not problems, problems
