@@ -1185,15 +1185,19 @@ namespace {
 // 128 x 128 / 256 x 128 / 256 x 256 tiles: four layers of 8192 with 700 / 1024
 // rows 457 / 428 / -, 536 / 487 / 568; four of 4096 with 1500 / 2048 rows
 // 240 / 223 / 307, 285 / 259 / 309; three of 2048 with 2000 rows 77 / 87 / 131.
+// No 256 x 128 tiles where their padded rows would take an intermediate to 4 GB.
 int chain_tile(int64_t M, int layers, const int64_t* dims, int cus) {
-  int64_t narrowest = dims[1];
+  int64_t narrowest = dims[1], widest_z = 0;
   bool wide = true;
   for (int l = 1; l <= layers; ++l) {
     narrowest = std::min(narrowest, dims[l]);
     wide = wide && dims[l] % 256 == 0;
+    if (l < layers) widest_z = std::max(widest_z, dims[l]);
   }
-  if (wide && (int64_t)ceil_div(M, 256) * (narrowest / 256) >= cus) return 2;
-  if ((int64_t)ceil_div(M, 256) * (narrowest / 128) >= cus * 3 / 4) return 3;
+  const int64_t mb256 = ceil_div(M, 256);
+  if (wide && mb256 * (narrowest / 256) >= cus) return 2;
+  const bool fits = (uint64_t)(mb256 * 256) * (uint64_t)widest_z * 2 < (uint64_t)1 << 32;
+  if (mb256 * (narrowest / 128) >= cus * 3 / 4 && fits) return 3;
   return (int64_t)ceil_div(M, 128) * (narrowest / 128) < cus ? 1 : 0;
 }
 
