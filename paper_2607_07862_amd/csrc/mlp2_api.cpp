@@ -1185,7 +1185,15 @@ namespace {
 // 128 x 128 / 256 x 128 / 256 x 256 tiles: four layers of 8192 with 700 / 1024
 // rows 457 / 428 / -, 536 / 487 / 568; four of 4096 with 1500 / 2048 rows
 // 240 / 223 / 307, 285 / 259 / 309; three of 2048 with 2000 rows 77 / 87 / 131.
-// No 256 x 128 tiles where their padded rows would take an intermediate to 4 GB.
+// No 256 x 128 tiles
+//   * where they need more rounds of the CUs than 128 x 128 tiles, two to a CU
+//     (two layers, 128 x 128 / 256 x 128: 600 x 12288 400 / 472, 600 x 21888
+//     1317 / 1414, 1 x 40960 1511 / 1724; with as many rounds 1100 x 8192
+//     376 / 344, 200 x 32896 1550 / 1347);
+//   * up to 64 rows, where 64 x 64 tiles are the alternative (two layers of
+//     24576, 64 x 64 / 256 x 128: 1 row 577 / 649, 64 rows 601 / 657, but 65
+//     rows 840 / 640);
+//   * where their padded rows would take an intermediate to 4 GB.
 int chain_tile(int64_t M, int layers, const int64_t* dims, int cus) {
   int64_t narrowest = dims[1], widest_z = 0;
   bool wide = true;
@@ -1196,9 +1204,10 @@ int chain_tile(int64_t M, int layers, const int64_t* dims, int cus) {
   }
   const int64_t mb256 = ceil_div(M, 256);
   if (wide && mb256 * (narrowest / 256) >= cus) return 2;
+  const int64_t pair = mb256 * (narrowest / 128), t128 = (int64_t)ceil_div(M, 128) * (narrowest / 128);
   const bool fits = (uint64_t)(mb256 * 256) * (uint64_t)widest_z * 2 < (uint64_t)1 << 32;
-  if (mb256 * (narrowest / 128) >= cus * 3 / 4 && fits) return 3;
-  return (int64_t)ceil_div(M, 128) * (narrowest / 128) < cus ? 1 : 0;
+  if (pair >= cus * 3 / 4 && ceil_div(pair, cus) <= ceil_div(t128, 2 * cus) && (M > 64 || t128 >= cus) && fits) return 3;
+  return t128 < cus ? 1 : 0;
 }
 
 // Multiply-adds per launch group of a chain (see chain_group_rows).

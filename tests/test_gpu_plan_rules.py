@@ -11,6 +11,28 @@ from _gpu import assert_matches_oracle
 pytestmark = pytest.mark.gpu
 
 
+# (M, equal widths, work-groups per CU of the chain's tile: 64 x 64 and 128 x 128 tiles two, 256 x 128 one)
+CHAINS = [
+    (64, 24576, 2),   # 64 x 64: few rows
+    (65, 24576, 1),   # 192 tiles of 256 x 128, three quarters of the CUs
+    (64, 32768, 1),   # few rows, but 64 x 64 tiles are no alternative
+    (128, 40960, 2),  # 320 tiles of 256 x 128 would be a second round, 320 of 128 x 128 fit one
+    (256, 40960, 1),  # 640 of 128 x 128: two rounds either way
+]
+
+
+@pytest.mark.parametrize("M,D,per_cu", CHAINS, ids=[f"{c[0]}x{c[1]}" for c in CHAINS])
+def test_chain_tile(lib, M, D, per_cu):
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    if cus != 256:
+        pytest.skip("the lines are drawn for 256 CUs")
+    print(f"\n[chain tile] {M} x {D}", flush=True)
+    plan = B.ChainPlan(M, [D, D, D], 1)
+    tiles128 = 2 * -(-M // 128) * (D // 128)
+    assert plan.grid() == (cus if per_cu == 1 else min(2 * cus, tiles128 * (4 if tiles128 < 2 * cus else 1)))
+    plan.close()
+
+
 def test_chain_whose_256_row_padding_would_pass_4_gb(lib):
     """126080 rows are 985 blocks of 128, an odd number: with 256-row tiles the intermediate's padded rows reach 4 GB."""
     M, dims = 126080, [128, 17024, 128]
