@@ -375,7 +375,13 @@ TileChoice choose_tiles(int64_t M, int64_t H, int64_t F, int nb, int cus) {
   // items that 128-column tiles of an N-wide GEMM give with K ranges of 768
   auto fill = [](int64_t N, int64_t K) { return ceil_div(N, 128) * std::max<int64_t>(1, K / 768); };
   const bool wide = nb == 1 && fill(F, H) >= 192 && fill(H, F) >= 192;
-  if (M <= 32) return {32, 64, nb == 1 && fill(H, F) >= 128 ? 128 : 64, 4, 4};
+  if (M <= 32) {
+    // More 64-column GEMM1 tiles than CUs would be a second round of items:
+    // 128 columns then (32 rows, 64 / 128: 8192 x 18432 140 / 122 us, 4096 x
+    // 16640 64.5 / 55.0, 704 x 20480 31.7 / 28.7, 512 x 16640 22.2 / 21.5).
+    const int bn1 = nb == 1 && ceil_div(F, 64) > cus ? 128 : 64;
+    return {32, bn1, nb == 1 && fill(H, F) >= 128 ? 128 : 64, 4, 4};
+  }
   if (M <= 64) {
     if (wide) return {64, 128, 128, 4, 4};
     // Too few 64-row tiles for a quarter of the CUs: 32-row tiles (64 x 512 x 2048: 14.7 -> 12.2 us).

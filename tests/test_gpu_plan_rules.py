@@ -11,6 +11,24 @@ from _gpu import assert_matches_oracle
 pytestmark = pytest.mark.gpu
 
 
+# (M, H, F, activation, tile rows, columns of GEMM1 and GEMM2, ring, waves)
+PLANS = [
+    # up to 32 rows: 64-column GEMM1 tiles up to one per CU
+    (32, 8192, 16384, 1, (32, 64, 128, 4, 4)),
+    (32, 8192, 16448, 1, (32, 128, 128, 4, 4)),
+]
+
+
+@pytest.mark.parametrize("M,H,F,act,want", PLANS, ids=["x".join(map(str, c[:4])) for c in PLANS])
+def test_plan_tiles(lib, M, H, F, act, want):
+    if torch.cuda.get_device_properties(0).multi_processor_count != 256:
+        pytest.skip("the lines are drawn for 256 CUs")
+    plan = B.Plan(M, H, F, act)
+    info = plan.info()
+    assert tuple(info[k] for k in ("bm", "bn1", "bn2", "stages", "waves")) == want, info
+    plan.close()
+
+
 # (M, equal widths, work-groups per CU of the chain's tile: 64 x 64 and 128 x 128 tiles two, 256 x 128 one)
 CHAINS = [
     (64, 24576, 2),   # 64 x 64: few rows
