@@ -371,6 +371,8 @@ TileChoice many_row_tiles(int64_t M, int64_t H, int64_t F, int nb, int cus) {
 //     34.2, 6144 x 1280 31.1 / 37.3, 4096 x 4096 49.5 / 46.9, 4096 x 14336 115 / 88
 //   224 rows, 128-row tiles / quadrant tiles: 2048 x 5632 40.1 / 63.5, 8192 x
 //     3584 89 / 109, 4096 x 14336 137 / 117
+//   200 rows, 128-row / 256-row tiles: 1024 x 1024 28.7 / 53.6, 512 x 1024
+//     22.0 / 38.2, 64 x 1472 20.2 / 33.0
 TileChoice choose_tiles(int64_t M, int64_t H, int64_t F, int nb, int cus) {
   // items that 128-column tiles of an N-wide GEMM give with K ranges of 768
   auto fill = [](int64_t N, int64_t K) { return ceil_div(N, 128) * std::max<int64_t>(1, K / 768); };
@@ -393,8 +395,7 @@ TileChoice choose_tiles(int64_t M, int64_t H, int64_t F, int nb, int cus) {
   }
   if (M <= 256) {
     if (nb == 1) return {128, 128, 128, 4, 8};
-    // (the smallest products keep the tiles that the parity tests pin)
-    if (H * F >= (int64_t)2 << 20 && H * F < (int64_t)40 << 20) return {128, 64, 128, 4, 4};
+    if (H * F < (int64_t)40 << 20) return {128, 64, 128, 4, 4};
     // 128 columns of each of Wg and Wu per tile, GEMM2 as two 128-column
     // halves: half the activation bytes per weight byte of 64-column tiles
     // (70B gated MLP, 256 rows: 600 -> 410 us with a plain mainloop).

@@ -39,8 +39,12 @@ SMALL = [
     (129, 256, 384, 2, {"bm": 128, "splitk1": 2}),
     (200, 320, 640, 2, None),
     (140, 256, 384, 0, {"splitk1": 2, "splitk2": 3}),
-    # 129..256 rows, SwiGLU, H a multiple of 128: the default plan's 256-row
-    # tiles with the GEMM2 tile run as two halves of the GEMM1 tile's width
+    # 129..256 rows, SwiGLU, H a multiple of 128: the 256-row tiles with the
+    # GEMM2 tile run as two halves of the GEMM1 tile's width
+    (200, 1024, 1024, 2, {"waves": 8, "bm": 256, "bn1": 128, "bn2": 256, "stages": 2}),
+    (256, 512, 768, 2, {"waves": 8, "bm": 256, "bn1": 128, "bn2": 256, "stages": 2}),
+    (200, 384, 640, 2, {"bm": 256, "bn1": 64, "bn2": 128, "stages": 3}),
+    # the same sizes through the default plan
     (200, 1024, 1024, 2, None),
     (256, 512, 768, 2, None),
     (200, 384, 640, 2, None),
@@ -76,10 +80,10 @@ def test_small_shapes_against_full_oracle(lib, M, H, F, act, tuning):
     d = I.make_inputs(M, H, F, act, seed=M * 7 + H + F)
     g = device_inputs(d)
     plan = B.Plan(M, H, F, act, tuning)
-    if act == 2 and 128 < M <= 256 and H % 128 == 0 and tuning is None:
+    if act == 2 and 128 < M <= 256 and tuning and tuning.get("bm") == 256 and "splitk1" not in tuning and "bk" not in tuning:
         info = plan.info()
         # the GEMM2 tile runs as two halves of the GEMM1 tile's width: eight waves
-        # of 128 + 128 columns where H allows, else four waves of 64 + 64
+        # of 128 + 128 columns, or four waves of 64 + 64
         want = (256, 256, 8) if H % 256 == 0 and F % 128 == 0 else (256, 128, 4)
         assert (info["bm"], info["bn2"], info["waves"]) == want, info
         assert info["bn2"] == 2 * info["bn1"], info

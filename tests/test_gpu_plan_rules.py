@@ -13,6 +13,10 @@ pytestmark = pytest.mark.gpu
 
 # (M, H, F, activation, tile rows, columns of GEMM1 and GEMM2, ring, waves)
 PLANS = [
+    # 129 to 256 rows, gated: 128-row tiles from the smallest product on
+    (200, 64, 1472, 2, (128, 64, 128, 4, 4)),
+    (129, 1024, 1024, 2, (128, 64, 128, 4, 4)),
+    (256, 4096, 14336, 2, (256, 128, 256, 2, 8)),
     # up to 32 rows: 64-column GEMM1 tiles up to one per CU
     (32, 8192, 16384, 1, (32, 64, 128, 4, 4)),
     (32, 8192, 16448, 1, (32, 128, 128, 4, 4)),
