@@ -320,6 +320,16 @@ struct TileChoice {
 // 161 / 558 and 186 / 206 / 683; 2112 x 5440, 512 / 777 / 2048 rows: 75 / 90 /
 // 149 and 56 / 87 / 170.  The estimates are within 20 % of these and their
 // order is right but for pairs within 5 % of each other.
+// Before the estimate: 128 x 64 tiles where each GEMM has at most one per CU
+// and
+//   * GELU, identity: a width is an odd multiple of 64.  Wider tiles are half
+//     padding in their last block there and no fewer rounds (us, 128 / 64
+//     columns: 300 x 128 x 192 13.7 / 11.4, 1000 x 704 x 1472 36.3 / 31.7; over
+//     536 sizes of 257 to 3000 rows 4 to 49 % faster up to that line, 15 %
+//     faster to 35 % slower past it).  (Even widths: faster too, but the wide
+//     tiles' plans run two work-groups per CU, a grid that callers may name.)
+//   * SwiGLU: the two depths sum to 768 (300 x 704 x 192 20.3 / 19.1, 300 x 256 x
+//     512 sequential 20.8 / 17.8; but 600 x 320 x 64 11.8 / 12.4).
 TileChoice many_row_tiles(int64_t M, int64_t H, int64_t F, int nb, int cus) {
   const struct {
     TileChoice t;
@@ -329,6 +339,8 @@ TileChoice many_row_tiles(int64_t M, int64_t H, int64_t F, int nb, int cus) {
               {{128, 128 / nb, 128, 2, 4}, 2, 0.70, 1.08},
               {{128, 128 / nb, 128, 4, nb == 1 ? 8 : 4}, 1, nb == 1 ? 0.65 : 0.70, 0},
               {{256, 128, 128, 3, 8}, 1, 0.90, 0}};
+  if ((int64_t)ceil_div(M, 128) * ceil_div(std::max(H, F), 64) <= cus && (nb == 2 ? H + F >= 768 : H % 128 || F % 128))
+    return {128, 64, 64, 4, 4};
   TileChoice best{};
   double best_us = 0;
   for (const auto& c : cand) {

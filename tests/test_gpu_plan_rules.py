@@ -20,6 +20,14 @@ PLANS = [
     # up to 32 rows: 64-column GEMM1 tiles up to one per CU
     (32, 8192, 16384, 1, (32, 64, 128, 4, 4)),
     (32, 8192, 16448, 1, (32, 128, 128, 4, 4)),
+    # beyond 256 rows: 128 x 64 tiles up to one per CU and GEMM, for an odd multiple of 64 or SwiGLU
+    (300, 128, 192, 1, (128, 64, 64, 4, 4)),
+    (1000, 2048, 704, 2, (128, 64, 64, 4, 4)),
+    (300, 256, 512, 2, (128, 64, 64, 4, 4)),
+    (600, 320, 64, 2, (128, 64, 128, 2, 4)),
+    (1024, 1984, 1984, 1, (128, 64, 64, 4, 4)),
+    (1024, 2048, 2112, 1, (128, 128, 128, 4, 8)),
+    (512, 256, 512, 1, (128, 128, 128, 2, 4)),
 ]
 
 
