@@ -698,12 +698,15 @@ int configure_plan(mlp2_plan_s* p, int64_t M, int64_t H, int64_t F, int act, con
   const int gran = std::max(mlp2::kBK, p->kc.bk);  // split-K parts hold whole stages
   // Items wanted: the launch's slots; for a streaming plan one per CU, with K
   // ranges of at least 768, or 512 where that leaves most CUs idle (32 rows:
-  // 6144 x 1280 20.6 us with 512, 19.0 with 768; 512 x 1472 12.9 and 14.3).
+  // 6144 x 1280 20.6 us with 512, 19.0 with 768; 512 x 1472 12.9 and 14.3);
+  // 448 beyond 64 rows, whose stages take longer (128 x 128 x 1472 16.7 us in
+  // two ranges, 15.4 in three).
   const bool streams = !tuned && M <= 256;
   const int want1 = (streams ? 1 : occ[0]) * p->num_cus, want2 = (streams ? 1 : occ[1]) * p->num_cus;
   if (streams) {
-    min_k1 = tiles1 * std::max<int64_t>(1, H / 768) < p->num_cus / 4 ? 512 : 768;
-    min_k2 = tiles2 * std::max<int64_t>(1, F / 768) < p->num_cus / 4 ? 512 : 768;
+    const int few = M > 64 ? 448 : 512;
+    min_k1 = tiles1 * std::max<int64_t>(1, H / 768) < p->num_cus / 4 ? few : 768;
+    min_k2 = tiles2 * std::max<int64_t>(1, F / 768) < p->num_cus / 4 ? few : 768;
   }
   if (tz.splitk1) {
     p->kc1 = (int)align_up((size_t)ceil_div(H, tz.splitk1), gran);

@@ -41,6 +41,14 @@ def test_plan_tiles(lib, M, H, F, act, want):
     plan.close()
 
 
+@pytest.mark.parametrize("M,parts", [(64, 2), (65, 3), (128, 3)])
+def test_plan_splits_a_lone_tile(lib, M, parts):
+    """One GEMM2 column block over 1472 rows of W2: ranges of at least 512, of 448 beyond 64 rows."""
+    plan = B.Plan(M, 64, 1472, 1)
+    assert plan.info()["splitk2"] == parts, plan.info()
+    plan.close()
+
+
 # (M, equal widths, work-groups per CU of the chain's tile: 64 x 64 and 128 x 128 tiles two, 256 x 128 one)
 CHAINS = [
     (64, 24576, 2),   # 64 x 64: few rows
