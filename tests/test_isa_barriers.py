@@ -225,3 +225,39 @@ def test_no_kernel_keeps_values_in_scratch_memory(asm):
     assert set(sizes) == set(ks)
     problems = {n: sizes[n] for n, b in ks.items() if int(sizes[n]) or "scratch_" in b}
     assert not problems, problems
+
+
+def mainloop_drains(body):
+    """Waits on vector memory that the compiler (not the kernels' own asm) put into a loop of matrix products.
+
+    The mainloops keep several stages of direct-to-LDS loads in flight and wait for the oldest by asm; a wait that the
+    compiler adds, for a register it believes a load may still write, empties the ring in every stage.  Loops that
+    load or store otherwise (the waits for ready counters, the item loop) are not mainloops."""
+    lines, own, in_asm = [], [], False
+    for l in body.splitlines():
+        if "#ASMSTART" in l or "#ASMEND" in l:
+            in_asm = "#ASMSTART" in l
+        l = l.split(";")[0].strip()
+        if l and (l.startswith(".LBB") or not l.startswith((".", "#"))):
+            lines.append(l)
+            own.append(in_asm)
+    at = {l[:-1]: i for i, l in enumerate(lines) if l.startswith(".LBB")}
+    bad = []
+    for i, l in enumerate(lines):
+        m = re.match(r"s_c?branch\w*\s+(\.LBB\w+)", l)
+        if not m or at[m.group(1)] > i:
+            continue
+        loop = range(at[m.group(1)], i)
+        text = [lines[j] for j in loop]
+        if not any(t.startswith("v_mfma") for t in text):
+            continue
+        if any(re.match(r"(global_load_dword|global_store|global_atomic|buffer_|scratch_)", t) for t in text):
+            continue
+        bad += [lines[j] for j in loop if lines[j].startswith("s_waitcnt") and "vmcnt" in lines[j] and not own[j]]
+    return bad
+
+
+def test_mainloops_wait_for_their_loads_by_their_own_counts(asm):
+    ks = kernels(asm)
+    problems = {n: v[:3] for n, b in ks.items() if (v := mainloop_drains(b))}
+    assert not problems, problems
