@@ -452,13 +452,22 @@ __device__ __forceinline__ void finish_kernel(const Args& a, bool roles, uint32_
 // any grid with at least one work-group per list, whatever the residency.
 //
 //   PHASE_WORKQUEUE: GEMM1 items by rank as in PHASE_GEMM1; a work-group whose
-//                    claim runs past them pops GEMM2 units from the device
-//                    workqueue until every unit of the run is claimed.  It
-//                    pops only once every GEMM1 item is claimed, and GEMM1
-//                    items never wait, so every producer finishes and every
-//                    claimed queue slot is filled: no deadlock either.  Claims
-//                    past the units are the reduction items: they wait for
-//                    units that running work-groups have popped.
+//                    claim runs past its list's ranks pops GEMM2 units from
+//                    the device workqueue, then reduction items.  Claim list
+//                    l hands out the queue slots congruent to l modulo the
+//                    lists in increasing order, and past the run's units the
+//                    reduction items likewise.  A list's claims thus go
+//                    through three classes in order, and each class waits
+//                    only for the ones before it: GEMM1 items never wait, and
+//                    an unclaimed one is reached by its list's work-groups,
+//                    which hold earlier GEMM1 items only; so all of them
+//                    finish, every unit is pushed and every slot fills.  An
+//                    unclaimed slot then is reached likewise (its list's
+//                    work-groups hold GEMM1 items or filled slots, and no
+//                    reduction item yet), so all units finish, and with them
+//                    all that the reduction items wait for, whichever list
+//                    ran those units.  As in the other phases this takes one
+//                    work-group per list that comes to run.
 
 //   PHASE_SENTINEL:  the pipelined rank table and claims, with the Lamport-
 //                    style synchronisation of Sec. V-A: GEMM1 items store Z at

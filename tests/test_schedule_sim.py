@@ -250,18 +250,24 @@ def test_xcd_grouped_deal_is_a_permutation_of_whole_column_waves(Mb, N, wave):
             assert len({t % Mb for t in tiles}) == 8 and len({t // Mb for t in tiles}) == 8
 
 
-def simulate_workqueue(Mb, Nb1, Nb2, S1, S2, grid, seed, k_ranges=None, order="auto", late_start=0):
+def simulate_workqueue(Mb, Nb1, Nb2, S1, S2, grid, seed, k_ranges=None, order="auto", late_start=0, red=0,
+                       reductions_first=False):
     """Step simulation of the workqueue mode (Sec. III-A.2-3 scheduling).
 
     GEMM1 items are claimed by rank through the claim lists (the first
     min(grid, items) ranks taken without tickets, as the host arranges);
-    a work-group whose claim runs past them takes the next queue slot and
-    waits until a unit is there.  A GEMM2 unit enters the queue when the last
+    a work-group whose claim runs past them takes the next queue slot of its
+    list (list l of L: slots l, l + L, ...) and waits until a unit is there;
+    past the units the same claims are reduction items (`red` slices per
+    tile), which wait until every part of their tile has run.  A GEMM2 unit enters the queue when the last
     part of the last GEMM1 tile it reads finishes (its scoreboard reaches its
     producer count).  `k_ranges[s]` lists the Z column blocks part s reads
     (default: even shares); parts of neighbouring ranges may share a block.
     Returns the units in run order with their start step and the step at
-    which their producers were all done, or None on deadlock."""
+    which their producers were all done, or None on deadlock (after 20 steps
+    in which no work-group did anything but wait, every duration being at most
+    6).  `reductions_first`: lists hand their reduction items out before their
+    units, which must deadlock."""
     rng = random.Random(seed)
     lists = claim_lists(grid)
     items1 = [(t, s) for t in column_first_tiles(Mb, Nb1, order) for s in range(S1)]
@@ -277,8 +283,11 @@ def simulate_workqueue(Mb, Nb1, Nb2, S1, S2, grid, seed, k_ranges=None, order="a
             users.setdefault(t, []).append(u)
     board = {u: 0 for u in units}
     parts = {}
-    queue, head = [], [0]
+    queue, head = [], [0] * lists
     ready_at, ran = {}, []
+    n_red = Mb * Nb2 * red
+    parts_left = {tile: S2 for tile in range(Mb * Nb2)}
+    reduced = set()
     first_static = min(grid, len(items1))
     ticket = [0] * lists
     skip = [len(range(l, first_static, lists)) for l in range(lists)]
@@ -294,8 +303,10 @@ def simulate_workqueue(Mb, Nb1, Nb2, S1, S2, grid, seed, k_ranges=None, order="a
     for g in range(grid):
         r = g if g < first_static else claim(g)
         wgs.append(["g1", r, rng.randint(1, 6), rng.randint(0, late_start)])
+    idle = 0
     for step in range(200000):
         if all(w[0] == "done" for w in wgs):
+            assert len(reduced) == n_red
             return ran
         progressed = False
         for g, w in enumerate(wgs):
@@ -303,8 +314,8 @@ def simulate_workqueue(Mb, Nb1, Nb2, S1, S2, grid, seed, k_ranges=None, order="a
             if phase == "done" or step < w[3]:
                 progressed |= phase != "done"
                 continue
-            progressed = True
             if phase == "g1":
+                progressed = True
                 if w[1] >= len(items1):
                     w[0], w[1] = "pop", None
                     continue
@@ -322,22 +333,35 @@ def simulate_workqueue(Mb, Nb1, Nb2, S1, S2, grid, seed, k_ranges=None, order="a
                 w[1], w[2] = claim(g), rng.randint(1, 6)
             elif phase == "pop":
                 if w[1] is None:
-                    w[1] = head[0]
-                    head[0] += 1
-                if w[1] >= len(units):
+                    progressed = True
+                    l = g % lists
+                    h = l + lists * head[l]
+                    head[l] += 1
+                    if reductions_first and h < len(units) + n_red:
+                        h = h + len(units) if h < n_red else h - n_red
+                    w[1] = h
+                if w[1] >= len(units) + n_red:
                     w[0] = "done"
+                elif w[1] >= len(units):  # a reduction item: its tile's parts have all run?
+                    r = w[1] - len(units)
+                    if parts_left[r // red] == 0:
+                        assert r not in reduced
+                        reduced.add(r)
+                        w[0], w[2] = "red", rng.randint(1, 6)
                 elif w[1] < len(queue):  # the slot is filled
                     u = queue[w[1]]
                     ran.append((u, step, ready_at[u]))
                     w[0], w[1], w[2] = "g2", u, rng.randint(1, 6)
-                else:
-                    progressed = any(x[0] in ("g1", "g2") for x in wgs) or progressed
-            elif phase == "g2":
+            else:  # a unit or a reduction item that runs
+                progressed = True
                 if w[2] > 0:
                     w[2] -= 1
                 else:
+                    if phase == "g2":
+                        parts_left[w[1][0]] -= 1
                     w[0], w[1] = "pop", None
-        if not progressed:
+        idle = 0 if progressed else idle + 1
+        if idle > 20:
             return None
     return None
 
@@ -352,6 +376,19 @@ def test_workqueue_schedule_runs_every_unit_after_its_producers(Mb, Nb1, Nb2, S1
             parts = len({s for _, s in (u for u, _, _ in ran)})
             assert sorted(u for u, _, _ in ran) == sorted((t, s) for t in range(Mb * Nb2) for s in range(parts))
             assert all(start >= ready for _, start, ready in ran)
+
+
+@pytest.mark.parametrize("Mb,Nb1,Nb2,S1,S2", CASES)
+def test_workqueue_schedule_ends_with_reduction_items_claimed_per_list(Mb, Nb1, Nb2, S1, S2):
+    for grid in (1, 2, 3, 8, 9, 17, 40):  # from one work-group per list on
+        for seed in range(3):
+            ran = simulate_workqueue(Mb, Nb1, Nb2, S1, S2, grid, seed, late_start=20 if seed else 0, red=2)
+            assert ran is not None and all(start >= ready for _, start, ready in ran), (grid, seed)
+
+
+def test_workqueue_schedule_that_hands_reduction_items_out_first_deadlocks():
+    assert simulate_workqueue(2, 8, 4, 1, 2, 4, 0, red=2) is not None
+    assert simulate_workqueue(2, 8, 4, 1, 2, 4, 0, red=2, reductions_first=True) is None
 
 
 def test_workqueue_schedule_with_parts_sharing_a_column_block():
