@@ -306,15 +306,15 @@ __device__ __forceinline__ int swz_b(int k) {
                : "memory")
 __device__ __forceinline__ void dma16(const void* base, uint32_t voff, uint32_t lds_addr) { MLP2_DMA16(""); }
 
-// The same load at device scope (sc1, the scope bit of the compiler's own
-// agent-scope atomic loads): it reads the device's point of coherence rather
-// than a line the consumer's XCD L2 may hold.  The sentinel mode's consumers
-// read the intermediate this way, since no release and acquire order it.
 // The same load with the non-temporal hint (a streamed operand read once).
 __device__ __forceinline__ void dma16_nt(const void* base, uint32_t voff, uint32_t lds_addr) {
   MLP2_DMA16(" nt");
 }
 
+// The same load at device scope (sc1, the scope bit of the compiler's own
+// agent-scope atomic loads): it reads the device's point of coherence rather
+// than a line the consumer's XCD L2 may hold.  The sentinel mode's consumers
+// read the intermediate this way, since no release and acquire order it.
 __device__ __forceinline__ void dma16_coherent(const void* base, uint32_t voff, uint32_t lds_addr) {
   MLP2_DMA16(" sc1");
 }
@@ -930,9 +930,10 @@ __device__ __forceinline__ void mainloop(const uint16_t* __restrict__ A, long ld
   // per stage: in the plain stage loop (every tile but the four-wave tiles
   // with three or more stages, below) an item that waits runs its stages
   // in the weights-first loop until its wait has seen every producer of its K
-  // range complete, then in the activation-first loop (gated 396 -> 388 us,
-  // prefill 440 -> 421 us pipelined; a choice per stage inside one loop made
-  // the one-launch kernels much slower: decode 74 -> 113 us).
+  // range complete, then in the activation-first loop (pipelined, with the
+  // 256-row tiles in this loop, before they had one of their own: gated 396
+  // -> 388 us, prefill 440 -> 421; a choice per stage inside one loop made the
+  // one-launch kernels much slower: decode 74 -> 113 us).
   auto issue = [&](int st, auto weights_first) {
     const int k = kbeg + st * T::BK;
     const uint32_t sbase = lds_base + (uint32_t)((st % T::NS) * SB);

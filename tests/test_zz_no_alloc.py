@@ -36,7 +36,7 @@ def _noalloc(M, H, act, g, mode):
 
 @pytest.mark.parametrize("mode", [B.MODE_TILE_PIPELINED, B.MODE_SEQUENTIAL, B.MODE_WORKQUEUE])
 def test_two_calls_in_a_row_match_the_planned_run(lib, mode):
-    big = (160, 1024, 2048, 1)     # 160 rows: 256-row tiles, split-K in both GEMMs
+    big = (160, 1024, 2048, 1)     # 160 rows: 128 x 128 tiles, split-K in both GEMMs
     small = (40, 512, 1024, 2)     # then fewer rows, narrower, SwiGLU
     outs = []
     for (M, H, F, act), seed in ((big, 11), (small, 12)):
