@@ -2,10 +2,12 @@
 
 Without a tile tuning the last column block of a GEMM may be narrower than
 its tile: the loads of columns past the end are clamped and their stores
-skipped.  Every tile family meets such widths here (with one 64-column
-remainder, and narrower than one tile), in every mode against the sequential
-mode's bits and the fp64 oracle; Y stands between guard rows that must stay
-as they were.
+skipped.  Every tile family that a plan chooses meets such widths here (with
+one 64-column remainder, and narrower than one tile; tiles of 64 columns and
+widths they divide beside them), in every mode against the sequential mode's
+bits and the fp64 oracle; Y stands between guard rows that must stay as they
+were.  Each case names the tile it is about, so a change of the choice cannot
+take it away unseen.
 """
 import pytest
 import torch
@@ -19,29 +21,39 @@ from _gpu import assert_bit_equal, assert_matches_oracle, device_inputs
 pytestmark = pytest.mark.gpu
 
 CASES = [
-    # M, H, F, act
-    (5, 1088, 4416, 1),     # 32-row tiles
-    (50, 192, 1472, 2),
-    (60, 8256, 3520, 0),    # 64-row tiles of 128 columns
-    (100, 8256, 3520, 1),   # 128-row tiles of 128 columns over eight waves
-    (120, 1088, 2112, 2),
-    (250, 1088, 1472, 1),
-    (250, 1600, 1472, 2),
-    (300, 320, 192, 1),     # 128 x 128 tiles beyond 256 rows
-    (300, 320, 192, 2),
-    (2100, 2112, 1344, 0),  # quadrant tiles
-    (1030, 1344, 5440, 2),
+    # M, H, F, act, the tile it is about: rows, columns of GEMM1 and GEMM2, ring, waves
+    (5, 1088, 4416, 1, (32, 64, 64, 4, 4)),
+    (50, 192, 1472, 2, (32, 64, 64, 4, 4)),
+    (20, 704, 16448, 1, (32, 128, 64, 4, 4)),
+    (60, 8256, 3520, 0, (64, 128, 128, 4, 4)),
+    (100, 8256, 3520, 1, (128, 128, 128, 4, 8)),
+    (120, 1088, 2112, 2, (64, 64, 128, 4, 4)),
+    (250, 1088, 1472, 1, (128, 128, 128, 4, 8)),
+    (250, 1600, 1472, 2, (128, 64, 128, 4, 4)),
+    (300, 320, 192, 1, (128, 64, 64, 4, 4)),
+    (300, 320, 192, 2, (128, 64, 128, 2, 4)),
+    (2100, 2112, 1344, 0, (128, 128, 128, 4, 8)),
+    (1030, 1344, 5440, 2, (128, 64, 128, 2, 4)),
+    (600, 8256, 8256, 1, (128, 128, 128, 2, 4)),
+    # quadrant tiles; the last gated GEMM2 block's second half lies past H, wholly or exactly
+    (2048, 2112, 5440, 0, (256, 256, 256, 2, 8)),
+    (2048, 2112, 5440, 2, (256, 128, 256, 2, 8)),
+    (2048, 2176, 5440, 2, (256, 128, 256, 2, 8)),
+    (1030, 8256, 3520, 0, (256, 256, 256, 2, 8)),
+    # pair tiles
+    (1024, 8256, 8256, 1, (256, 128, 128, 3, 8)),
 ]
 
 
-@pytest.mark.parametrize("M,H,F,act", CASES, ids=["x".join(map(str, c)) for c in CASES])
-def test_ragged_widths_in_every_mode(lib, M, H, F, act):
+@pytest.mark.parametrize("M,H,F,act,tile", CASES, ids=["x".join(map(str, c[:4])) for c in CASES])
+def test_ragged_widths_in_every_mode(lib, M, H, F, act, tile):
     d = I.make_inputs(M, H, F, act, seed=M + H + F + act)
     g = device_inputs(d)
     plan = B.Plan(M, H, F, act)
     info = plan.info()
     print(f"\n[ragged] {M}x{H}x{F} act={act} {info['bm']}x{info['bn1']} {info['bn2']} splits {info['splitk1']} {info['splitk2']}", flush=True)
-    assert F % info["bn1"] or H % info["bn2"] or info["bn1"] == 64, info
+    if info["num_cus"] == 256:  # the choices are drawn for 256 CUs
+        assert tuple(info[k] for k in ("bm", "bn1", "bn2", "stages", "waves")) == tile, info
     outs = {}
     for mode in ("sequential", "tile_pipelined", "workqueue", "sentinel"):
         box = torch.full((M + 2, H), 7.0, dtype=torch.bfloat16, device="cuda")
