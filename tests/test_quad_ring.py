@@ -1,91 +1,192 @@
 """The ping-pong mainloops (256 x 256 quadrant tiles, 256 x 128 pair tiles): ring protocol on the CPU, stage counts on the GPU.
 
-* CPU: a model of the slot program (the half-tile requests, waits, reads and
-  barriers of the leading and the trailing waves) shows, for every stage
-  count, that no half tile is read before every wave's pieces of it have
+* CPU: the loops' slot program (the half-tile requests, waits, reads and
+  barriers of the leading and the trailing waves) is read from the kernel
+  source and shows, for every stage count, that no half tile is read before every wave's pieces of it have
   arrived and a barrier has passed, and that no ring slot is requested again
   before every wave's reads of it are complete and a barrier has passed.
 * GPU: items of one, two, three and more stages (split-K ranges) of both
   operand forms, ragged rows, every mode bit-equal and within the oracle's bound.
 """
+import os
+import re
+
 import pytest
 
-HALVES = ("A0", "B0", "B1", "A1")
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+SRC = os.path.join(ROOT, "paper_2607_07862_amd", "csrc", "mlp2_device.hpp")
 
 
-def program(nk, blocks):
-    """One wave's slots: each a list of ("req", half, stage) / ("read", half, stage) / ("vm", n) / ("lgkm",);
-    every slot ends in a barrier."""
-    two = nk > 1
-    if blocks:
-        pro = [[("req", "B0", 0), ("req", "B1", 0)] + ([("req", "B0", 1), ("req", "B1", 1)] if two else [])]
-        pro.append([("req", "A0", 0), ("req", "A1", 0)] + ([("req", "A0", 1)] if two else []) + [("vm", 0)])
-    else:
-        pro = [[("req", h, 0) for h in HALVES] + ([("req", h, 1) for h in HALVES[:3]] if two else []) + [("vm", 10 if two else 4)]]
-    body = [[("read", "A0", 0), ("lgkm",)]]  # joined to the first memory slot below
-    for it in range(nk):
-        left = min(2, nk - 1 - it)
-        m0 = ([("req", "A1", it + 1)] if left else []) + [("read", "B0", it), ("vm", 10 if left else 2)]
-        m1 = ([("req", "A0", it + 2)] if left == 2 else []) + [("read", "B1", it), ("vm", (0, 8, 10)[left])]
-        m2 = ([("req", "B0", it + 2)] if left == 2 else []) + [("read", "A1", it)] + ([("vm", 10 if left == 2 else 6)] if left else [])
-        m3 = ([("req", "B1", it + 2)] if left == 2 else []) + ([("read", "A0", it + 1), ("vm", 10 if left == 2 else 4)] if left else [])
-        for m in (m0, m1, m2, m3):
-            body += [m, [("lgkm",)]]
-    first = body.pop(0)
-    return pro, first, body
+# ------------------------------------------------------------------ the loops, read from the kernel source
+
+def closing(text, i):
+    """Index of the bracket that closes the one at text[i]."""
+    pairs = {"{": "}", "(": ")"}
+    depth = 0
+    for j in range(i, len(text)):
+        depth += (text[j] == text[i]) - (text[j] == pairs[text[i]])
+        if depth == 0:
+            return j
+    raise ValueError("unbalanced")
 
 
-def pair_program(nk, blocks):
-    """The same of the 256 x 128 tile: two phases a stage, three stages of each half tile."""
-    if blocks:
-        pro = [[("req", "B0", st) for st in range(min(nk, 2))],
-               [("req", h, st) for st in range(min(nk, 2)) for h in ("A0", "A1")] + ([("req", "A0", 2)] if nk > 2 else []) + [("vm", 0)]]
-    else:
-        pro = [[("req", h, st) for st in range(min(nk, 2)) for h in ("A0", "B0", "A1")] + ([("req", "A0", 2)] if nk > 2 else [])
-               + [("vm", 10 if nk > 2 else 8 if nk == 2 else 2)]]
-    body = []
-    for it in range(nk):
-        left = min(3, nk - 1 - it)
-        m0 = ([("req", "B0", it + 2)] if left >= 2 else []) + [("read", "B0", it), ("vm", (0, 4, 8, 8)[left])]
-        m1 = ([("req", "A1", it + 2)] if left >= 2 else []) + ([("req", "A0", it + 3)] if left >= 3 else []) + [("read", "A1", it)]
-        m1 += [("read", "A0", it + 1), ("vm", (0, 2, 8, 10)[left])] if left else []
-        body += [m0, [("lgkm",)], m1, [("lgkm",)]]
-    return pro, [("read", "A0", 0), ("lgkm",)], body
+def loop_source(name):
+    """(stage lambda's body, what follows it up to the function's end), without comments."""
+    text = re.sub(r"//[^\n]*", "", open(SRC).read())
+    start = text.index("{", text.index(f"void {name}("))
+    body = text[start + 1:closing(text, start)]
+    at = body.index("auto stage = [&]")
+    o = body.index("{", at)
+    c = closing(body, o)
+    return body[o + 1:c], body[c + 2:]
 
 
-def timeline(nk, blocks, trailing, pair):
-    """(real slot, op) in order: the trailing waves pass one extra barrier after the first read."""
-    pro, first, body = (pair_program if pair else program)(nk, blocks)
-    slots = [list(s) for s in pro]
-    if trailing:
-        slots += [first] + body
-    else:
-        slots += [first + body[0]] + body[1:]
-    return [(i, op) for i, s in enumerate(slots) for op in s]
+def parse(text):
+    """Statements as ("if", condition, then, else), ("for", condition, body) and ("do", text)."""
+    out, i = [], 0
+
+    def unit(i):  # one statement or block from i: (statements, next index)
+        while text[i].isspace():
+            i += 1
+        if text[i] == "{":
+            c = closing(text, i)
+            return parse(text[i + 1:c]), c + 1
+        m = re.match(r"(if\s*(?:constexpr)?|for)\s*\(", text[i:])
+        if m:
+            o = i + m.end() - 1
+            c = closing(text, o)
+            head = text[o + 1:c]
+            then, j = unit(c + 1)
+            if m.group(1) == "for":
+                return [("for", head, then)], j
+            e = re.match(r"\s*else\b", text[j:])
+            if not e:
+                return [("if", head, then, [])], j
+            other, j = unit(j + e.end())
+            return [("if", head, then, other)], j
+        j = text.index(";", i)
+        return [("do", " ".join(text[i:j].split()))], j + 1
+
+    while text[i:].strip():
+        part, i = unit(i)
+        out += part
+    return out
 
 
-def check(nk, blocks, pair):
-    halves = ("A0", "B0", "A1") if pair else HALVES
+def value(expr, env):
+    """A C expression of integers and conditions."""
+    expr = expr.replace("Wait::kBlocks", "blocks")
+    m = re.match(r"([^?]*)\?([^:]*):(.*)$", expr)
+    if m:
+        return value(m.group(2), env) if value(m.group(1), env) else value(m.group(3), env)
+    expr = re.sub(r"!(?!=)", " not ", expr.replace("&&", " and ").replace("||", " or "))
+    return int(eval(expr.strip(), {}, dict(env)))
+
+
+def program(source, nk, blocks, trailing, pair):
+    """One wave's operations in order: ("req", half, stage, ring slot), ("read", half, ring slot), ("vm", n), ("lgkm",), ("bar",)."""
+    stage_body, rest = (parse(t) for t in source)
+    ops = []
+    env = {"nk": nk, "blocks": int(blocks), "trailing": int(trailing), "wave": 4 if trailing else 0, "r": 0}
+
+    def call(name, args):
+        v = [value(a, env) if re.fullmatch(r"[\w\s+\-]+", a) and not re.match(r"[xw][ab01]?$", a.strip()) else None for a in args]
+        if name == "load_a":
+            ops.append(("req", f"A{v[0]}", v[1], v[2] if pair else v[1] & 1))
+        elif name == "load_b":
+            ops.append(("req", "B0", v[0], v[1]) if pair else ("req", f"B{v[0]}", v[1], v[1] & 1))
+        elif name == "read_a":
+            ops.append(("read", f"A{v[1]}", v[2] if pair else v[2] & 1))
+        elif name == "read_b":
+            ops.append(("read", "B0", v[0]) if pair else ("read", f"B{v[1]}", v[2] & 1))
+        elif name == "slot_end":
+            ops.append(("bar",))
+        elif name == "products_begin":
+            ops.append(("lgkm",))
+        elif name == "products_end":
+            ops.append(("bar",))
+        elif name == "products":
+            ops.extend([("lgkm",), ("bar",)])
+        elif name not in ("mma", "__syncthreads"):
+            raise ValueError(f"unknown call {name}")
+
+    def do(t):
+        m = re.match(r"stage\((.*), int_constant<(\d)>\(\)\)$", t)
+        if m:
+            env["it"], env["LEFT"] = value(m.group(1), env), int(m.group(2))
+            run(stage_body)
+            return
+        m = re.match(r"vm_traced\(int_constant<(.*)>\(\)\)$", t) or re.match(r"wait_vm<(\d+)>\(\)$", t)
+        if m:
+            # the ternary's conditions hold ">=": the constant is what stands between the outer angle brackets
+            ops.append(("vm", value(m.group(1), env)))
+            return
+        if t.startswith("wait.") or t.startswith("constexpr int LEFT") or t.startswith("const int k ="):
+            return
+        if t == "__builtin_amdgcn_s_waitcnt(0xC07F)":
+            ops.append(("lgkm",))
+            return
+        m = re.match(r"(?:const (?:int|bool) |int )?(\w+ = .*)$", t)
+        if m:
+            for a in m.group(1).split(","):
+                k, e = a.split("=", 1)
+                env[k.strip()] = value(e, env)
+            return
+        m = re.match(r"(\w+)\((.*)\)$", t)
+        call(m.group(1), m.group(2).split(","))
+
+    def run(nodes):
+        for n in nodes:
+            if n[0] == "do":
+                do(n[1])
+            elif n[0] == "if":
+                run(n[2] if value(n[1], env) else n[3])
+            else:
+                init, cond, step = n[1].split(";")
+                assert step.strip() == "++it" and init.strip() == "int it = 0", n[1]
+                i = 0
+                while value(cond, {**env, "it": i}):
+                    assert len(n[2]) == 1
+                    do(n[2][0][1].replace("(it,", f"({i},"))
+                    i += 1
+
+    run(rest)
+    return ops
+
+
+def check(source, nk, blocks, pair):
+    """Every half tile is read once, after every wave's pieces of it have arrived and a barrier, and its ring slot
+    requested again only after every wave's reads are complete and a barrier."""
+    halves = ("A0", "B0", "A1") if pair else ("A0", "B0", "B1", "A1")
     deep = 3 if pair else 2  # stages of a half tile in the ring
     reads, arrived, done, req = {}, {}, {}, {}
+    bars = []
     for wave in (0, 1):
-        pending, unread = [], []
-        for slot, op in timeline(nk, blocks, wave == 1, pair):
-            if op[0] == "req":
+        slot, pending, unread, holds = 0, [], [], {}
+        for op in program(source, nk, blocks, wave == 1, pair):
+            if op[0] == "bar":
+                slot += 1
+            elif op[0] == "req":
+                assert op[3] == op[2] % deep, op
                 pending += [(op[1], op[2])] * 2  # two pieces per wave and half tile
                 req[wave, op[1], op[2]] = slot
+                holds[op[1], op[3]] = op[2]
             elif op[0] == "vm":
                 while len(pending) > op[1]:
                     arrived[(wave, *pending.pop(0))] = slot
             elif op[0] == "read":
-                reads[wave, op[1], op[2]] = slot
-                unread.append((wave, op[1], op[2]))
+                key = (wave, op[1], holds[op[1], op[2]])
+                assert key not in reads, f"{key} read twice"
+                reads[key] = slot
+                unread.append(key)
             else:  # lgkm: the fragment reads so far are in registers
                 for r in unread:
                     done[r] = slot
                 unread = []
         assert not pending, (nk, blocks, pending)  # nothing lands after the loop
         assert not unread
+        bars.append(slot)
+    assert bars[0] == bars[1], bars  # every wave passes as many barriers
     want = {(w, h, s) for w in (0, 1) for h in halves for s in range(nk)}
     assert set(reads) == want and set(req) == want and set(done) == want
     for (w, h, s), at in reads.items():
@@ -99,7 +200,25 @@ def check(nk, blocks, pair):
 @pytest.mark.parametrize("pair", [False, True])
 @pytest.mark.parametrize("blocks", [False, True])
 def test_the_ring_protocol_for_every_stage_count(blocks, pair):
-    assert all(check(nk, blocks, pair) for nk in range(1, 14))
+    source = loop_source("mainloop_pair" if pair else "mainloop_quad")
+    assert all(check(source, nk, blocks, pair) for nk in range(1, 14))
+
+
+@pytest.mark.parametrize("pair", [False, True])
+def test_no_looser_wait_keeps_the_ring_protocol(pair):
+    """Each wait of the stage, loosened by one half tile (two pieces) in the text, breaks the protocol."""
+    stage, rest = loop_source("mainloop_pair" if pair else "mainloop_quad")
+    waits = [m for m in re.finditer(r"vm_traced\(int_constant<(.*?)>\(\)\)", stage)]
+    assert len(waits) == (2 if pair else 4)
+    broken = 0
+    for m in waits:
+        looser = stage[:m.start(1)] + re.sub(r"(?<=[?:] )\d+", lambda d: str(int(d.group()) + 2), m.group(1)) + stage[m.end(1):]
+        try:
+            for nk in range(1, 14):
+                check((looser, rest), nk, False, pair)
+        except (AssertionError, KeyError):
+            broken += 1
+    assert broken == len(waits)
 
 
 CASES = [
