@@ -636,7 +636,9 @@ int configure_plan(mlp2_plan_s* p, int64_t M, int64_t H, int64_t F, int act, con
   // the last column block may be narrower than the tile (its loads are
   // clamped, its stores guarded): 777 x 2112 x 5440, whose widths are odd
   // multiples of 64, 86 us with 64-column tiles, 60 us with 128.
-  const bool tuned = small_ws || tz.bm || tz.bn1 || tz.bn2 || tz.stages || tz.waves || tz.bk || tz.splitk1 || tz.splitk2 || tz.grid || tz.p1;
+  // (The hint forced on names the tiles that are built with it.)
+  const bool tuned = small_ws || tz.bm || tz.bn1 || tz.bn2 || tz.stages || tz.waves || tz.bk || tz.splitk1 || tz.splitk2 || tz.grid ||
+                     tz.p1 || tz.weights_nt == 1;
   int min_k1 = 256, min_k2 = 256;  // shallowest K range of one split-K part
   const TileChoice tc = tuned ? tuned_tiles(M, H, F, nb, num_cus, &min_k1, &min_k2) : choose_tiles(M, H, F, nb, num_cus);
   const int pref[4] = {tc.bm, tc.bn1, tc.bn2, tc.ns};

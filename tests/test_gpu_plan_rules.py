@@ -41,6 +41,21 @@ def test_plan_tiles(lib, M, H, F, act, want):
     plan.close()
 
 
+@pytest.mark.parametrize("M,H,F,built", [(129, 256, 256, True), (198, 6400, 2048, True), (256, 4096, 14336, True),
+                                         (100, 4096, 14336, False), (300, 1024, 3584, False), (200, 6400, 2112, False)])
+def test_the_forced_weight_hint_takes_the_tiles_built_with_it(lib, M, H, F, built):
+    """Gated plans of 129 to 256 rows whose widths the hinted tile divides, at any size; refused elsewhere."""
+    if not built:
+        with pytest.raises(B.Mlp2Error) as e:
+            B.Plan(M, H, F, 2, {"weights_nt": 1})
+        assert e.value.code == B.ERR_UNSUPPORTED
+        return
+    plan = B.Plan(M, H, F, 2, {"weights_nt": 1})
+    info = plan.info()
+    assert (info["bm"], info["bn1"], info["bn2"], info["weights_nt"]) == (256, 128, 256, 1), info
+    plan.close()
+
+
 @pytest.mark.parametrize("M,parts", [(64, 2), (65, 3), (128, 3)])
 def test_plan_splits_a_lone_tile(lib, M, parts):
     """One GEMM2 column block over 1472 rows of W2: ranges of at least 512, of 448 beyond 64 rows."""
