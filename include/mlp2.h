@@ -309,7 +309,9 @@ int mlp2_run_noalloc(int64_t M, int64_t H, int64_t F, int act, int dtype, const 
  * accumulation; the intermediates are stored as bf16 in the plan's
  * workspace.  Items are output tiles over their whole K: 256 x 256 (eight
  * waves) when every width D_1 .. D_L is a multiple of 256 and the narrowest
- * layer has a 256-row tile per CU, else 128 x 128, or 64 x 64 when the
+ * layer has a 256-row tile per CU; else 256 x 128 (eight waves) when that layer
+ * has one for three quarters of the CUs, beyond 64 rows, and 128 x 128 tiles
+ * would need no fewer rounds of the CUs; else 128 x 128, or 64 x 64 when the
  * narrowest layer would have fewer 128-row tiles than CUs; each layer's
  * tiles are dealt to the XCDs in sub-blocks of rows and columns.  Chains of
  * many rows run as back-to-back launches over row groups of about 2.2 T

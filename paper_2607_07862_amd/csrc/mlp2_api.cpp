@@ -307,19 +307,21 @@ struct TileChoice {
 // x 128 tiles in two four-wave work-groups per CU (0.70 us alone on the CU,
 // 1.08 beside the other), or 128 x 128 tiles with a deep ring, one work-group
 // per CU (0.65 us; SwiGLU 0.70), or 256 x 128 pair tiles (0.90 us; not
-// SwiGLU), whichever gemm_us finds fastest.  Measured
-// us, in that order, GELU:
-//   4096 x 14336, 300 / 512 / 777 / 2048 rows: 140 / 142 / 201 / 376, 138 /
-//     145 / 251 / 468, 156 / 166 / - / -
-//   4096 x 4096, 300 / 512 / 777 rows: two per CU 65 / 67 / 90, one 53 / 59 /
-//     80, pair - / 68 / 94
-//   2048 x 5632, 300 / 1000 rows: two per CU 51 / 64, one 46 / 76, pair - / 64
-//   8192 x 8192, 1024 rows: quadrant 251, pair 245
-//   2112 x 5440, 777 / 1536 / 2048 rows: 88 / 94 / 105, 60 / 81 / 106
+// SwiGLU), whichever gemm_us finds fastest.  Measured us, in that order, GELU,
+// pipelined, the chosen one starred:
+//   4096 x 14336, 300 rows 135 / 133* / 147 / 117, 512 139 / 131 / 162 / 121*,
+//     777 201* / 257 / 265 / 224, 2048 380* / 471 / 578 / 436
+//   4096 x 4096, 300 rows 107 / 64 / 53* / 66, 512 102 / 61 / 57* / 66, 777 112
+//     / 81 / 79* / 84, 1300 120 / 98 / 99* / 103
+//   2048 x 5632, 300 rows 77 / 51 / 45* / 51, 1000 82 / 63 / 76 / 61*
+//   8192 x 8192, 600 rows 202 / 211* / 242 / 199, 1024 253 / 263 / 325 / 237*
+//   2112 x 5440, 777 rows 84 / 60* / 76 / 64, 1536 94 / 79 / 103 / 80*, 2048
+//     104* / 103 / 157 / 104
 // SwiGLU, quadrant and two per CU: 4096 x 14336, 300 / 512 / 2048 rows: 159 /
 // 161 / 558 and 186 / 206 / 683; 2112 x 5440, 512 / 777 / 2048 rows: 75 / 90 /
-// 149 and 56 / 87 / 170.  The estimates are within 20 % of these and their
-// order is right but for pairs within 5 % of each other.
+// 149 and 56 / 87 / 170.  The estimates themselves are rough (94 us for the 75
+// of 512 x 2112 x 5440); the choice is within 6 % of the fastest at these
+// sizes but for 300 x 4096 x 14336, where the pair tile is 12 % faster.
 // Before the estimate: 128 x 64 tiles where each GEMM has at most one per CU
 // and
 //   * GELU, identity: a width is an odd multiple of 64.  Wider tiles are half
@@ -654,12 +656,12 @@ int configure_plan(mlp2_plan_s* p, int64_t M, int64_t H, int64_t F, int act, con
   };
   // Weight loads with the non-temporal hint once the two weight matrices
   // together exceed the 256 MiB last-level cache: streamed weights then stop
-  // displacing the lines the activation and Z loads reuse (70B gated MLP,
-  // 1.4 GB of weights, back-to-back runs: 390 -> 378 us pipelined,
-  // 405 -> 390 us sequential; after a 1 GiB flush: 389 -> 393 us pipelined,
-  // 405 -> 398 us sequential).  Where the weights fit, a warm run reads part
-  // of them from that cache, and the hint loses it (decode 80 -> 101 us,
-  // prefill 430 -> 452 us): off; and off past 256 rows, where every row block
+  // displacing the lines the activation and Z loads reuse (70B gated MLP, 256
+  // rows, 1.4 GB of weights, back-to-back runs without / with: 325 / 316 us
+  // pipelined, 328 / 317 us sequential; after a 1 GiB flush: 354 / 339 and 356 /
+  // 341).  Where the weights fit, a warm run reads part of them from that
+  // cache, and the hint loses it (decode 80 -> 101 us, prefill 430 -> 452 us,
+  // with the plain loops): off; and off past 256 rows, where every row block
   // reads the weights again (gated 8192 x 28672 with 512 / 1024 / 2048 rows:
   // 592 / 1120 / 2034 us with the hint, 585 / 1098 / 1995 without).
   const bool big_weights = M <= 256 && (uint64_t)(nb + 1) * (uint64_t)H * (uint64_t)F * 2 > ((uint64_t)256 << 20);

@@ -1318,9 +1318,9 @@ __device__ __forceinline__ void reduce_units(const float* base, long tile, int S
 }
 
 // The parts a round loads: no more than the tile has, up to 8 (two parts in
-// rounds of eight read part 1 seven times: 2048 x 4096 x 14336, whose last
-// parts sum 512 KB a tile in the workqueue mode, 433 -> 390 us).  `f` is
-// called with the count as a constant.
+// rounds of eight read part 1 seven times: 2048 x 4096 x 14336 in the workqueue
+// mode, when the last part to arrive still summed the 512 KB of a tile alone,
+// 433 -> 390 us).  `f` is called with the count as a constant.
 template <class F>
 __device__ __forceinline__ void with_round(int S, F&& f) {
   if (S <= 2) f(int_constant<2>());
